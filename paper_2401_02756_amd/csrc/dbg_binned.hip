@@ -27,69 +27,15 @@
 // with a 32-bit LDS atomic add (Algorithm 3's increment), and writes the
 // segment back.  No global atomic is issued per k-mer; a segment is only ever
 // touched by its owner, so plain loads and stores move it.
-#include "dbg_device.h"
+#include "dbg_records.h"
 
 #include <algorithm>
 
 namespace dbgk {
 namespace {
 
-constexpr uint32_t kSkipMask = kErrBase | kErrInval | kErrRange | kErrSkip;
-static_assert((kSegSlots & (kSegSlots - 1)) == 0, "segment size must be a power of two");
 static_assert(kBinTile <= 4096 && kRefTile <= 4096, "ranks are packed into 12 bits");
 static_assert(kMaxD1 % kBinBlock == 0 && kMaxFan % kRefBlock == 0, "bucket scans");
-
-__device__ __forceinline__ uint64_t lds_load64(const uint64_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-__device__ __forceinline__ uint32_t lds_add32(uint32_t *p, uint32_t v) {
-    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Long keys (33 <= k <= 63, so K < 2^124) as (kh = K >> 64 < 2^60, kl):
-// two Feistel rounds give the image (ih < 2^60, il): il = kl ^ mix64(kh),
-// then ih = kh ^ (il * kWideMul) >> 4.  ih takes the place of a short key's
-// image (its top bits are the segment digits) and il's low bits are the
-// home slot; each round undoes itself given the other half.
-constexpr uint64_t kWideMul = 0xD1B54A32D192ED03ull;  // odd
-
-__device__ __forceinline__ void wide_image(uint64_t kh, uint64_t kl, uint64_t &ih, uint64_t &il) {
-    il = kl ^ mix64(kh);
-    ih = kh ^ ((il * kWideMul) >> 4);
-}
-
-__device__ __forceinline__ void wide_key(uint64_t ih, uint64_t il, uint64_t &kh, uint64_t &kl) {
-    kh = ih ^ ((il * kWideMul) >> 4);
-    kl = il ^ mix64(kh);
-}
-
-// A window record: RW = 1, one word image << 3 | sink << 2 | letter; RW = 2
-// (long keys), that word built from ih, then il.  Both start with the word
-// that carries the segment digits and the flags.
-template <uint32_t RW> struct RecOf;
-template <> struct RecOf<1> {
-    using T = uint64_t;
-    static __device__ __forceinline__ uint64_t head(uint64_t r) { return r; }
-    static __device__ __forceinline__ uint64_t none() { return ~0ull; }
-};
-template <> struct RecOf<2> {
-    using T = ulonglong2;
-    static __device__ __forceinline__ uint64_t head(ulonglong2 r) { return r.x; }
-    static __device__ __forceinline__ ulonglong2 none() { return make_ulonglong2(~0ull, 0); }
-};
-
-
-// Last index i in [0, n) with base(i) <= x, for a non-decreasing base.
-template <typename F>
-__device__ __forceinline__ uint64_t last_le(uint64_t n, uint64_t x, F base) {
-    uint64_t lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if (base(mid) <= x) lo = mid; else hi = mid;
-    }
-    return lo;
-}
 
 // XCD-aware order of a persistent loop over n tiles.  Workgroups are
 // dispatched to the 8 XCDs round-robin (workgroup b runs on XCD b % 8), and
@@ -209,54 +155,6 @@ __device__ __forceinline__ void next_read(ReadCursor &c, const ReadStage &S, con
     c = ReadCursor{rp.wr1, rp.delta, kMapReads + 1};
 }
 
-// 64 bits starting `o` bits into the 192-bit big-endian word triple (o < 128).
-__device__ __forceinline__ uint64_t funnel3(uint64_t a, uint64_t b, uint64_t c, uint32_t o) {
-    if (o >= 64) {
-        a = b;
-        b = c;
-        o -= 64;
-    }
-    return o ? (a << o) | (b >> (64 - o)) : a;
-}
-
-// Rolling window state of one-word keys (k <= 31).  Consecutive windows of a
-// read share all but one base: the key of the next window is the key shifted
-// by one base, with the window's letter shifted in and its first base shifted
-// out.  The image multiplies the key by kKeyMul modulo 2^60, so with
-// x = key * kKeyMul mod 2^60 the next window's x is
-//   4 x + letter * kKeyMul - first * (4^(k-1) * kKeyMul)  (mod 2^60),
-// one shift-add of a table entry indexed by (first base, letter).  F holds
-// the 32 bases from the window's first on, L the 32 from its letter on, so a
-// thread rolls through up to 32 windows of one read without touching the
-// packed reads again.
-struct Roll {
-    uint64_t F, L, x;
-};
-
-// The state of the window whose first base is at position p of the packed
-// reads.  kshift = 64 - 2 (k - 1).
-__device__ __forceinline__ Roll roll_at(const uint64_t *__restrict__ packed, uint64_t p, uint32_t k,
-                                        uint32_t kshift) {
-    const uint64_t wb = p >> 5;
-    const uint64_t a = packed[wb], b = packed[wb + 1], c = packed[wb + 2];
-    const uint32_t o = (uint32_t)(p & 31) * 2;  // o + 2 (k - 1) <= 122: inside the triple
-    const uint64_t F = funnel3(a, b, c, o);
-    return Roll{F, funnel3(a, b, c, o + 2 * (k - 1)), ((F >> kshift) * kKeyMul) & kKey60};
-}
-
-// Table entry (first << 2 | letter): letter * kKeyMul - first * 4^(k-1) * kKeyMul, mod 2^60.
-__device__ __forceinline__ uint64_t roll_entry(uint32_t e, uint32_t k) {
-    const uint64_t out = (kKeyMul << (2 * (k - 1))) & kKey60;
-    return ((uint64_t)(e & 3u) * kKeyMul - (uint64_t)(e >> 2) * out) & kKey60;
-}
-
-__device__ __forceinline__ void roll_next(Roll &r, const uint64_t *s_roll) {
-    const uint32_t e = (uint32_t)(r.F >> 62) << 2 | (uint32_t)(r.L >> 62);
-    r.F <<= 2;
-    r.L <<= 2;
-    r.x = ((r.x << 2) + s_roll[e]) & kKey60;
-}
-
 // Scatter tiles count with tagged counters: s_cnt[j] starts at j << rb, so
 // the value a record's fetch-add returns is its tag, bucket << rb | rank, and
 // bucket j's count is s_cnt[j] - (j << rb) (rb = 12 for tiles of 4096
@@ -284,8 +182,6 @@ __device__ void bucket_starts(uint32_t *s_cnt, uint64_t *s_gbase, uint32_t n, ui
         }
     }
 }
-
-__host__ __device__ inline uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
 
 // ---------------------------------------------------------------- line-staged scatters
 //
@@ -610,7 +506,7 @@ __global__ __launch_bounds__(scatter_block(SHAPE, true, RW)) __attribute__((amdg
     R *rec1 = reinterpret_cast<R *>(rec1w);
     const uint32_t tid = threadIdx.x;
     const uint32_t m = args->m;
-    const uint64_t *__restrict__ off = args->off;
+    const uint64_t *__restrict__ off = as_global(args->off);
     const uint64_t chunks = tot->chunks1, chunk = tot->chunk1;
     const uint64_t off0 = off[0];
     // One flat loop over the tiles of this workgroup's chunks: only the chunk
@@ -1152,139 +1048,6 @@ __global__ void k_part_starts(const PassArgs *__restrict__ args, const Instance 
 
 // ---------------------------------------------------------------- reduce
 
-// Sum of v over the block; thread 0 adds it to *dst.  Whole block.
-__device__ void flush_block_sum(uint64_t v, uint64_t *dst, uint64_t *s_sum) {
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    if (threadIdx.x == 0) *s_sum = 0;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0 && v)
-        __hip_atomic_fetch_add(s_sum, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __syncthreads();
-    if (threadIdx.x == 0 && *s_sum) atomic_add_u64(dst, *s_sum);
-    __syncthreads();
-}
-
-constexpr uint32_t kReducePrefetch = 8;  // records a thread loads before using them
-constexpr uint64_t kNoRecord = ~0ull;     // no record: a record's first word stays below 2^63
-
-// Find-or-claim one record's vertex in the LDS segment and count its letter.
-// Returns false when the segment has no free slot for it.
-// home_mask: kSegSlots - 1, or 7 with the test hash (every key of a segment
-// then starts at one of its first eight slots).
-template <bool STATS>
-__device__ __forceinline__ bool reduce_record(uint64_t rec, uint64_t *s_key, uint32_t *s_cnt,
-                                              uint64_t &claims, uint32_t home_mask, ProbeStats &ps) {
-    const uint64_t img = rec >> 3;
-    const uint64_t tagv = img | kOccupied;
-    uint32_t s = seg_home(img) & home_mask;
-    uint32_t q = 0;
-    if constexpr (!STATS) {
-        // Each probe is one compare-and-swap of an empty slot to this key: it
-        // claims the slot if empty and otherwise returns the key it holds, so
-        // the loop has one exit test and no nested branch (10 % less reduce
-        // time than a load followed by a CAS on empty slots).  The statistics
-        // build below keeps the load, so that a CAS it issues is one that
-        // expected an empty slot and a failed one is a lost race.
-        uint64_t old;
-        for (;;) {
-            old = 0;
-            __hip_atomic_compare_exchange_strong(&s_key[s], &old, tagv, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (old == 0 || old == tagv) break;
-            if (++q == kSegSlots) return false;
-            s = (s + 1) & (kSegSlots - 1);
-        }
-        claims += old == 0 ? 1u : 0u;
-        if (!(rec & 4)) lds_add32(&s_cnt[4 * s + (uint32_t)(rec & 3)], 1u);
-        return true;
-    }
-    uint64_t cur = lds_load64(&s_key[s]);
-    // probe until the slot holds this key (found, or claimed here); the count
-    // is added once, after the loop
-    for (;;) {
-        if (cur == 0) {
-            uint64_t expected = 0;
-            __hip_atomic_compare_exchange_strong(&s_key[s], &expected, tagv, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (STATS) {
-                ++ps.cas;
-                ps.lost += expected != 0 ? 1u : 0u;
-            }
-            if (expected == 0) {
-                ++claims;
-                break;
-            }
-            cur = expected;
-        }
-        if (cur == tagv) break;
-        if (++q == kSegSlots) return false;
-        s = (s + 1) & (kSegSlots - 1);
-        cur = lds_load64(&s_key[s]);
-    }
-    if (STATS) ps.lookup(q + 1);
-    if (!(rec & 4)) lds_add32(&s_cnt[4 * s + (uint32_t)(rec & 3)], 1u);
-    return true;
-}
-
-// Long keys: a slot's key is two LDS words, hi (ih | kOccupied) and lo (il).
-// A slot is claimed by the CAS of hi; the claimer then stores lo and sets
-// kReady in hi.  A lane that finds its own hi without kReady has met a claim
-// in flight and reads the slot again (the claimer waits on nothing between
-// its CAS and those stores); with kReady set, lo decides whether the slot
-// is this key's.  Returns the slot, or kSegSlots when none is found.
-constexpr uint64_t kReady = 1ull << 62;
-constexpr uint32_t kMaxInFlightReads = 1u << 20;
-
-template <bool STATS>
-__device__ __forceinline__ uint32_t wide_slot(uint64_t tag, uint64_t lo, uint64_t *s_hi, uint64_t *s_lo,
-                                              bool &claimed, uint32_t home_mask, ProbeStats &ps) {
-    uint32_t s = seg_home(lo) & home_mask, waits = 0;
-    for (uint32_t q = 0;;) {
-        uint64_t cur = __hip_atomic_load(&s_hi[s], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (cur == 0) {
-            uint64_t expected = 0;
-            __hip_atomic_compare_exchange_strong(&s_hi[s], &expected, tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (STATS) {
-                ++ps.cas;
-                ps.lost += expected != 0 ? 1u : 0u;
-            }
-            if (expected == 0) {
-                __hip_atomic_store(&s_lo[s], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                __hip_atomic_store(&s_hi[s], tag | kReady, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                claimed = true;
-                if (STATS) ps.lookup(q + 1);
-                return s;
-            }
-            cur = expected;
-        }
-        if ((cur & ~kReady) == tag) {
-            if (!(cur & kReady)) {  // claim in flight: read the slot again
-                if (++waits > kMaxInFlightReads) return kSegSlots;
-                continue;
-            }
-            if (lds_load64(&s_lo[s]) == lo) {
-                if (STATS) ps.lookup(q + 1);
-                return s;
-            }
-        }
-        if (++q == kSegSlots) return kSegSlots;
-        s = (s + 1) & (kSegSlots - 1);
-    }
-}
-
-template <bool STATS>
-__device__ __forceinline__ bool reduce_record(ulonglong2 rec, uint64_t *s_key, uint32_t *s_cnt, uint64_t &claims,
-                                              uint32_t home_mask, ProbeStats &ps) {
-    bool claimed = false;
-    const uint32_t s =
-        wide_slot<STATS>((rec.x >> 3) | kOccupied, rec.y, s_key, s_key + kSegSlots, claimed, home_mask, ps);
-    if (s == kSegSlots) return false;
-    claims += claimed ? 1u : 0u;
-    if (!(rec.x & 4)) lds_add32(&s_cnt[4 * s + (uint32_t)(rec.x & 3)], 1u);
-    return true;
-}
-
 // One workgroup per segment.  The segment's hash slots live in LDS only: the
 // vertices the table already holds (packed at entries [0, seg_count)) are
 // re-inserted, every record of the segment is found-or-claimed and counted
@@ -1311,21 +1074,14 @@ __global__ __launch_bounds__(kReduceBlock) void k_reduce(const PassArgs *__restr
     static_assert(RW == 1 || EW == 4, "long keys take 32-byte entries");
     const uint32_t m = args->m;
     const uint64_t parts_total = args->parts_total;
-    // fused extraction (one instance): see the write-back
-    uint64_t *__restrict__ xkeys = args->xkeys;
-    uint4 *__restrict__ xcounts = reinterpret_cast<uint4 *>(args->xcounts);
-    const uint64_t xcap = args->xcap;
-    static_assert(kSegSlots % kReduceBlock == 0 && kReduceBlock % 64 == 0, "slot ranges per wavefront");
-    constexpr uint32_t kWaves = kReduceBlock / 64;
-    constexpr uint32_t kWaveSlots = kSegSlots / kWaves;  // slots compacted by one wavefront
     __shared__ uint64_t s_key[kSegSlots * RW];  // RW = 2: hi words, then lo words
     __shared__ __align__(16) uint32_t s_cnt[kSegSlots * 4];
     __shared__ uint64_t s_start[kStartsChunk + 2];
-    __shared__ uint32_t s_wave_n[kWaves];
+    __shared__ uint32_t s_wave_n[kReduceWaves];
     __shared__ uint64_t s_sum, s_xbase;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t home_mask = args->test_hash ? 7u : kSegSlots - 1;
-    ProbeStats ps, ps_old;  // ps_old: re-inserted vertices of earlier builds, not counted
+    ProbeStats ps;
     const uint64_t per_block = (parts_total + gridDim.x - 1) / gridDim.x;
     const uint64_t gp0 = min((uint64_t)blockIdx.x * per_block, parts_total);
     const uint64_t gp1 = min(gp0 + per_block, parts_total);
@@ -1378,30 +1134,8 @@ __global__ __launch_bounds__(kReduceBlock) void k_reduce(const PassArgs *__restr
         const uint64_t seg_idx = gp - in.part_base;
         uint64_t *seg = in.table + seg_idx * (uint64_t)kSegSlots * EW;
         // a skipped (rejected) instance has no records and its table is left untouched
-        const uint32_t n_old = (skip || in.fresh) ? 0u : min(in.seg_count[seg_idx], kSegSlots);
-        for (uint32_t e = tid; e < n_old; e += blockDim.x) {
-            // distinct keys: each claims its own slot, and nobody else touches
-            // that slot's counters before the next barrier
-            const uint64_t tagv = seg[e];
-            const uint4 cv = seg_counts<RW>(seg)[e];
-            if constexpr (RW == 2) {
-                bool claimed = false;
-                const uint32_t s =
-                    wide_slot<false>(tagv, seg[kSegSlots + e], s_key, s_key + kSegSlots, claimed, home_mask, ps_old);
-                if (s < kSegSlots) reinterpret_cast<uint4 *>(s_cnt)[s] = cv;
-                continue;
-            }
-            uint32_t s = seg_home(tagv) & home_mask;
-            for (uint32_t q = 0; q < kSegSlots; ++q) {
-                uint64_t expected = 0;
-                if (__hip_atomic_compare_exchange_strong(&s_key[s], &expected, tagv, __ATOMIC_RELAXED,
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                    reinterpret_cast<uint4 *>(s_cnt)[s] = cv;
-                    break;
-                }
-                s = (s + 1) & (kSegSlots - 1);
-            }
-        }
+        const uint32_t n_old = (skip || in.fresh) ? 0u : min(as_global(in.seg_count)[seg_idx], kSegSlots);
+        seg_reinsert<RW>(seg, n_old, s_key, s_cnt, home_mask);
         __syncthreads();
         bool full = false;
         for (uint64_t base = a;;) {
@@ -1430,74 +1164,20 @@ __global__ __launch_bounds__(kReduceBlock) void k_reduce(const PassArgs *__restr
         if (full) atomic_or_u32(&st[cur_inst].err, kErrFull);
         __syncthreads();
         if (skip) continue;  // uniform; LDS is still all zero
-        // write the occupied slots back packed: each wavefront compacts its
-        // own slot range with ballots, after one exchange of range totals
-        const uint32_t s0 = wave * kWaveSlots;
-        uint32_t mine = 0;
-        for (uint32_t c0w = 0; c0w < kWaveSlots; c0w += 64)
-            mine += (uint32_t)__popcll(__ballot(s_key[s0 + c0w + lane] != 0));
+        const uint32_t mine = seg_count_slots(s_key, lane, wave);
         if (lane == 0) s_wave_n[wave] = mine;
         __syncthreads();
-        uint32_t out = 0, total = 0;
-        for (uint32_t w2 = 0; w2 < kWaves; ++w2) {
-            const uint32_t nw = s_wave_n[w2];
-            out += w2 < wave ? nw : 0u;
-            total += nw;
-        }
-        // Fused extraction: the segment's vertices also go to the caller's
-        // arrays at [xbase, xbase + total), reserved with one device atomic
-        // whose latency the table write-back below hides.  The order of
-        // segments in the output is whatever order the reservations land in.
-        uint64_t xbase = 0;
-        if (xkeys && tid == 0)
-            xbase = __hip_atomic_fetch_add(&st[cur_inst].emitted, (uint64_t)total, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t out0 = out;
-        for (uint32_t c0w = 0; c0w < kWaveSlots; c0w += 64) {
-            const uint32_t s = s0 + c0w + lane;
-            const uint64_t tagv = s_key[s];
-            const uint64_t mask = __ballot(tagv != 0);
-            if (tagv) {
-                const uint32_t rank = (uint32_t)__popcll(mask & ((1ull << lane) - 1));
-                seg[out + rank] = tagv & ~kReady;
-                if (RW == 2) seg[kSegSlots + out + rank] = s_key[kSegSlots + s];
-                seg_counts<RW>(seg)[out + rank] = reinterpret_cast<const uint4 *>(s_cnt)[s];
-                if (!xkeys) {
-                    s_key[s] = 0;
-                    reinterpret_cast<uint4 *>(s_cnt)[s] = make_uint4(0, 0, 0, 0);
-                }
+        if (args->xkeys) {  // uniform; fused extraction: room for the segment's vertices
+            if (tid == 0) {
+                uint64_t n = 0;
+                for (uint32_t w = 0; w < kReduceWaves; ++w) n += s_wave_n[w];
+                s_xbase = __hip_atomic_fetch_add(&st[cur_inst].emitted, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            out += (uint32_t)__popcll(mask);
-        }
-        if (xkeys) {  // uniform
-            if (tid == 0) s_xbase = xbase;
             __syncthreads();
-            const uint64_t xb = s_xbase;
-            out = out0;
-            for (uint32_t c0w = 0; c0w < kWaveSlots; c0w += 64) {
-                const uint32_t s = s0 + c0w + lane;
-                const uint64_t tagv = s_key[s];
-                const uint64_t mask = __ballot(tagv != 0);
-                if (tagv) {
-                    const uint64_t o = xb + out + (uint32_t)__popcll(mask & ((1ull << lane) - 1));
-                    if (o < xcap) {
-                        if constexpr (RW == 1) {
-                            xkeys[o] = key_of_image(tagv & ~kOccupied);
-                        } else {  // two key words per record: K >> 64, K mod 2^64
-                            uint64_t kh, kl;
-                            wide_key(tagv & ~(kOccupied | kReady), s_key[kSegSlots + s], kh, kl);
-                            xkeys[2 * o] = kh;
-                            xkeys[2 * o + 1] = kl;
-                        }
-                        xcounts[o] = reinterpret_cast<const uint4 *>(s_cnt)[s];
-                    }
-                    s_key[s] = 0;
-                    reinterpret_cast<uint4 *>(s_cnt)[s] = make_uint4(0, 0, 0, 0);
-                }
-                out += (uint32_t)__popcll(mask);
-            }
         }
-        if (tid == 0) in.seg_count[seg_idx] = total;
+        const uint32_t total = seg_store<RW>(seg, s_key, s_cnt, s_wave_n, lane, wave, args->xkeys, args->xcounts,
+                                             args->xcap, s_xbase);
+        if (tid == 0) as_global(in.seg_count)[seg_idx] = total;
         __syncthreads();
     }
     flush_block_sum(my_claims, &st[cur_inst].claimed, &s_sum);

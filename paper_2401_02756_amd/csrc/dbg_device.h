@@ -8,6 +8,17 @@ namespace dbgk {
 
 constexpr uint64_t kAllOnes = ~0ull;
 
+// A pointer to device memory that was itself read from memory (an argument
+// block, a table of instances, LDS).  The compiler cannot see its address
+// space and would access it with flat instructions, which share the counter
+// of LDS operations: every wait for an LDS result, and so every barrier, then
+// waits for all such loads and stores to finish.
+template <typename T>
+__device__ __forceinline__ T *as_global(T *p) {
+    // by way of an integer: a cast there and back alone is dropped
+    return (T *)(__attribute__((address_space(1))) T *)reinterpret_cast<uintptr_t>(p);
+}
+
 // SplitMix64 output function (Steele, Lea, Flood, "Fast splittable
 // pseudorandom number generators", OOPSLA 2014): a bijective 64-bit mixer.
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {
@@ -92,6 +103,23 @@ __device__ __forceinline__ void wide_window(uint64_t x0, uint64_t x1, uint32_t k
     klo = r == 64 ? x0 : (x1 >> r) | (x0 << (64 - r));
     khi = r == 64 ? 0 : x0 >> r;
     letter = (uint32_t)(x1 >> (r - 2)) & 3u;
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+
+// Inclusive scan over the wavefront (all 64 lanes active): four row shifts,
+// then the row sums broadcast down.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    v = dpp_add<0x111, 0xf>(v);
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);
+    v = dpp_add<0x143, 0xc>(v);
+    return v;
 }
 
 __device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v) {

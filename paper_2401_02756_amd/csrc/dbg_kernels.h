@@ -238,6 +238,66 @@ struct BinBuffers {     // device scratch of one binned pass
     uint32_t shape1, shape2;
 };
 
+// Partition by sorted tiles (dbg_sorted.hip), the automatic shape of a binned
+// build: every tile of records is stored sorted by digit, with one row of
+// 16-bit offsets, and a digit's records are gathered from its pieces.
+constexpr uint32_t kSingleParts = 1024;  // tables of up to this many segments take one level
+static_assert(kSingleParts <= kMaxD1, "single-level tables: a bucket is a segment");
+constexpr uint32_t kSortGroup = 64;      // level-1 tiles whose offsets are transposed together
+
+struct SortPlan {       // per instance
+    uint64_t w_begin, w_end;  // its windows
+    uint64_t tiles;           // level-1 tiles (0: not built in this launch)
+    uint64_t tile_base;       // first level-1 tile
+    uint64_t groups;          // groups of kSortGroup tiles (0 when one level suffices)
+    uint64_t group_base;      // first group
+    uint64_t offt_base;       // first transposed offset (d1 x tiles, bucket-major)
+    uint64_t gsum_base;       // first group sum (d1 x groups, bucket-major)
+    uint64_t bucket_base;     // first level-1 bucket
+    uint64_t valid;           // nonzero: its offsets hold, so its reads may be looked at
+};
+
+struct SortBucket {     // per level-1 bucket of a two-level instance
+    uint64_t start, size;     // its records in the level-2 output
+    uint32_t inst, b;         // owning instance, bucket in it
+};
+
+struct SortTotals {
+    uint64_t tiles, buckets, groups;
+};
+
+struct SortBuffers {    // device scratch of one pass
+    SortPlan *plan;           // m
+    SortTotals *totals;
+    SortBucket *buckets;      // buckets_cap
+    uint64_t *tile2_base;     // buckets_cap + 1
+    uint64_t *tile_read;      // first read of each level-1 tile (tiles1_cap)
+    uint16_t *off1, *off2;    // offset rows (tiles1_cap x row1, tiles2_cap x row2)
+    uint32_t *offt;           // transposed offsets (d1_max x tiles1_cap)
+    uint32_t *gsum;           // group sums (d1_max x groups_cap)
+    uint64_t *gpre;           // and what lies before each group
+    uint64_t *rec1, *rec2;    // sorted tiles of records
+    uint64_t tiles1_cap, tiles2_cap, groups_cap, buckets_cap, parts_cap;
+    uint32_t d1_max, fan_max, row1, row2;
+    uint32_t tile1, tile2;    // records of a tile
+    uint32_t entry_words, rec_words;
+    uint32_t two_level;       // some instance needs the second level
+    uint32_t grid_reduce;     // persistent grid (sorted_grids)
+};
+
+// The scatter shapes that dbg_stats reports for automatic shapes (code of the
+// first | second << 8): big tiles, of 128 KB in a first level of many buckets;
+// a first level of long keys counts as big only there.
+constexpr uint32_t auto_shapes(uint32_t rec_words, uint32_t d1) {
+    return (rec_words == 1 ? (d1 > 384 ? 4u : 3u) : (d1 > 384 ? 3u : 1u)) | 3u << 8;
+}
+
+// Reserve the kernels' dynamic LDS and fill the grid size (no query happens
+// while a launch is being captured).
+void sorted_grids(int device, SortBuffers &sb);
+hipError_t launch_sorted(const PassArgs *args, const Instance *inst, const uint64_t *ws, InstStatus *st,
+                         const SortBuffers &sb, uint64_t n_cap, bool stats, hipStream_t s, hipEvent_t *marks);
+
 // Fill the grid sizes of bb from occupancy and its capacities.
 void binned_grids(int device, BinBuffers &bb);
 

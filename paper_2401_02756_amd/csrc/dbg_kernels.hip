@@ -31,7 +31,7 @@ __global__ void k_prepare(const PassArgs *__restrict__ args, Instance *inst, Ins
                           CallState *cs) {
     const uint32_t m = args->m;
     const uint64_t n = args->n_reads;
-    const uint64_t *off = args->off;
+    const uint64_t *off = as_global(args->off);
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < m) {
         st[i].err = inst[i].skip ? kErrSkip : 0u;
@@ -77,7 +77,7 @@ __global__ void k_gather_u64(const uint64_t *__restrict__ src, const uint64_t *_
 __global__ __launch_bounds__(256) void k_pack(const PassArgs *__restrict__ args,
                                              uint64_t *__restrict__ packed,
                                              const Instance *__restrict__ inst, InstStatus *st) {
-    const uint8_t *__restrict__ ascii = args->reads;
+    const uint8_t *__restrict__ ascii = as_global(args->reads);
     const uint64_t n = args->reads_len;
     const uint64_t n_words = packed_words(n);
     const uint32_t m = args->m;
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_local(
     const PassArgs *__restrict__ args, const Instance *__restrict__ inst, InstStatus *st,
     uint64_t *__restrict__ ws, uint64_t *__restrict__ partials, uint64_t *__restrict__ kpart) {
     __shared__ uint32_t s_t0, s_t1;
-    const uint64_t *__restrict__ off = args->off;
+    const uint64_t *__restrict__ off = as_global(args->off);
     const uint64_t n = args->n_reads, len = args->reads_len;
     const uint32_t m = args->m, check_ends = args->check_ends;
     const uint64_t rb = (uint64_t)blockIdx.x * kScanReads;
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(1024) void k_scan_partials(const PassArgs *__restri
 __global__ __launch_bounds__(kScanBlock) void k_scan_add(
     const PassArgs *__restrict__ args, const Instance *__restrict__ inst, uint64_t *__restrict__ ws,
     const uint64_t *__restrict__ partials, uint64_t *__restrict__ tile_read) {
-    const uint64_t *__restrict__ off = args->off;
+    const uint64_t *__restrict__ off = as_global(args->off);
     const uint64_t n = args->n_reads, len = args->reads_len, tile_cap = args->tile_cap;
     const uint32_t m = args->m, check_ends = args->check_ends, tile = args->tile;
     if ((uint64_t)blockIdx.x * kScanReads >= n) return;
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(1024) void k_build(const PassArgs *__restrict__ arg
                                                const uint64_t *__restrict__ ws,
                                                const uint64_t *__restrict__ tile_read,
                                                InstStatus *st, CallState *cs, uint32_t wpt) {
-    const uint64_t *__restrict__ off = args->off;
+    const uint64_t *__restrict__ off = as_global(args->off);
     const uint64_t n = args->n_reads;
     const uint32_t m = args->m;
     __shared__ uint64_t s_ws[kMapReads + 1];
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(1024) void k_build(const PassArgs *__restrict__ arg
     uint64_t cap0 = 0;
     uint32_t ew0 = 3, km1_0 = 0;
     if (SINGLE) {
-        tab0 = inst[0].table;
+        tab0 = as_global(inst[0].table);
         cap0 = inst[0].cap;
         ew0 = inst[0].entry_words;
         km1_0 = inst[0].k - 1;
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(1024) void k_build(const PassArgs *__restrict__ arg
             uint64_t cap = cap0;
             uint32_t ew = ew0;
             if (!SINGLE && win.valid) {
-                tab = inst[win.inst].table;
+                tab = as_global(inst[win.inst].table);
                 cap = inst[win.inst].cap;
                 ew = inst[win.inst].entry_words;
             }
@@ -665,7 +665,7 @@ __global__ __launch_bounds__(1024) void k_build_wide(const PassArgs *__restrict_
                                                     const uint64_t *__restrict__ ws,
                                                     const uint64_t *__restrict__ tile_read,
                                                     InstStatus *st, CallState *cs, uint32_t wpt) {
-    const uint64_t *__restrict__ off = args->off;
+    const uint64_t *__restrict__ off = as_global(args->off);
     const uint64_t n = args->n_reads;
     __shared__ uint64_t s_ws[kMapReads + 1];
     __shared__ uint64_t s_delta[kMapReads];
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(1024) void k_build_wide(const PassArgs *__restrict_
     const uint64_t off0 = n ? off[0] : 0;
     const uint64_t T = (uint64_t)blockDim.x * wpt;
     const uint64_t ntiles = (W + T - 1) / T;
-    uint64_t *tab = inst[0].table;
+    uint64_t *tab = as_global(inst[0].table);
     const uint64_t cap = inst[0].cap;
     const uint32_t km1 = inst[0].k - 1;
     if (inst[0].prior_inserts + st[0].inserts > 0xffffffffull) {

@@ -146,13 +146,16 @@ struct PassKey {
     int wide = 0;  // one instance with 32 < k <= 64, direct build
     uint32_t rw = 1;  // binned record words (2: long keys)
     uint32_t ew = 3;
+    int sorted = 0;   // binned, partitioned by sorted tiles (automatic scatter shapes)
+    uint32_t d1_two_cap = 0;  // most level-1 buckets of a graph that needs both levels (0: none does)
     uint32_t m_cap = 0, d1_cap = 0, fan_cap = 0;
     uint64_t n_cap = 0, len_cap = 0, parts_cap = 0, buckets_cap = 0;
     dbgk::BuildShape shape{};
     bool operator==(const PassKey &o) const {
         return binned == o.binned && stats == o.stats && bin_chunks == o.bin_chunks && bin_div == o.bin_div &&
                bin_shape1 == o.bin_shape1 && bin_shape2 == o.bin_shape2 &&
-               single == o.single && wide == o.wide && rw == o.rw && ew == o.ew &&
+               single == o.single && wide == o.wide && rw == o.rw && ew == o.ew && sorted == o.sorted &&
+               d1_two_cap == o.d1_two_cap &&
                m_cap == o.m_cap &&
                d1_cap == o.d1_cap && fan_cap == o.fan_cap && n_cap == o.n_cap && len_cap == o.len_cap &&
                parts_cap == o.parts_cap && buckets_cap == o.buckets_cap && shape.block == o.shape.block &&
@@ -160,11 +163,25 @@ struct PassKey {
     }
 };
 
+// Options of a pass besides its input: where its probe statistics go
+// (DBG_F_STATS; null: none kept) and whether keys take the test hash.
+struct PassOpts {
+    uint64_t *stats = nullptr;
+    uint32_t test_hash = 0;
+    uint32_t bin_chunks = 0, bin_div = 0, bin_shape1 = 0, bin_shape2 = 0;  // binned launch shape (0: defaults)
+};
+
 // Capacities of a pass over mm instances (host instances hi filled), n reads
 // and len bytes.
 inline PassKey pass_key(uint32_t mm, uint64_t n, uint64_t len, dbgk::BuildShape shape, bool binned,
-                        const Instance *hi) {
+                        const Instance *hi, const PassOpts &o) {
     PassKey k;
+    k.stats = o.stats != nullptr;
+    k.bin_chunks = o.bin_chunks;
+    k.bin_div = o.bin_div;
+    k.bin_shape1 = o.bin_shape1;
+    k.bin_shape2 = o.bin_shape2;
+    k.sorted = binned && !o.bin_shape1 && !o.bin_shape2;
     k.binned = binned ? 1 : 0;
     k.single = mm == 1 ? 1 : 0;
     k.shape = shape;
@@ -174,10 +191,11 @@ inline PassKey pass_key(uint32_t mm, uint64_t n, uint64_t len, dbgk::BuildShape 
     k.n_cap = size_class(n, 1024);
     k.len_cap = size_class(len, 4096);
     uint64_t P = 0, G1 = 0;
-    uint32_t d1max = 1, fanmax = 1;
+    uint32_t d1max = 1, fanmax = 1, d1two = 0;
     for (uint32_t i = 0; i < mm; ++i) {
         P += hi[i].parts;
         G1 += hi[i].d1;
+        if (hi[i].fan > 1) d1two = std::max(d1two, hi[i].d1);
         d1max = std::max(d1max, hi[i].d1);
         fanmax = std::max(fanmax, hi[i].fan);
         if (hi[i].parts) k.ew = hi[i].entry_words;
@@ -186,6 +204,7 @@ inline PassKey pass_key(uint32_t mm, uint64_t n, uint64_t len, dbgk::BuildShape 
         k.parts_cap = size_class(P, 64);
         k.buckets_cap = size_class(G1, 64);
         k.d1_cap = (uint32_t)std::min<uint64_t>(size_class(d1max, 16), dbgk::kMaxD1);
+        k.d1_two_cap = d1two ? (uint32_t)std::min<uint64_t>(size_class(d1two, 16), dbgk::kMaxD1) : 0;
         k.fan_cap = (uint32_t)std::min<uint64_t>(size_class(fanmax, 16), dbgk::kMaxFan);
     }
     return k;
@@ -211,6 +230,54 @@ inline void bin_caps(const PassKey &k, dbgk::BinBuffers &bb) {
     bb.entry_words = k.ew;
     bb.rec_words = k.rw;
 }
+
+// Records of a level-1 tile: 2048 for a small input (more workgroups, each
+// done sooner), else 64 KB of records, or 128 KB where a first level of many
+// buckets would leave pieces of a few records.  (The tile shapes and what each
+// measured: dbg_sorted.hip.)
+inline uint32_t sort_tile1(const PassKey &k) {
+    if (k.len_cap <= (1u << 21)) return 2048;
+    return (k.d1_two_cap > 384 ? 16384u : 8192u) / k.rw;
+}
+
+// Capacities (not pointers) of the sorted-tile scratch of a key.
+inline void sort_caps(const PassKey &k, dbgk::SortBuffers &sb) {
+    sb.tile1 = sort_tile1(k);
+    sb.tile2 = 16384 / k.rw;
+    sb.two_level = k.d1_two_cap != 0;
+    sb.tiles1_cap = k.len_cap / sb.tile1 + k.m_cap + 1;
+    sb.groups_cap = sb.tiles1_cap / dbgk::kSortGroup + k.m_cap + 1;
+    sb.tiles2_cap = k.len_cap / sb.tile2 + k.buckets_cap + 1;
+    sb.buckets_cap = k.buckets_cap;
+    sb.parts_cap = k.parts_cap;
+    sb.d1_max = k.d1_cap;
+    sb.fan_max = k.fan_cap;
+    sb.row1 = k.d1_cap + 2;
+    sb.row2 = k.fan_cap + 2;
+    sb.entry_words = k.ew;
+    sb.rec_words = k.rw;
+}
+
+// Byte sizes of the sorted-tile scratch (sb: sort_caps(k)).
+struct SortSizes {
+    uint64_t plan, totals, buckets, tile2_base, tile_read, off1, off2, offt, gsum, gpre, rec1, rec2;
+    SortSizes(const PassKey &k, const dbgk::SortBuffers &sb) {
+        const uint64_t two = sb.two_level ? 1 : 0;
+        plan = sizeof(dbgk::SortPlan) * k.m_cap;
+        totals = sizeof(dbgk::SortTotals);
+        buckets = two * sizeof(dbgk::SortBucket) * sb.buckets_cap;
+        tile2_base = two * 8 * (sb.buckets_cap + 1);
+        tile_read = 8 * sb.tiles1_cap;
+        off1 = 2ull * sb.row1 * sb.tiles1_cap;
+        off2 = two * 2 * sb.row2 * sb.tiles2_cap;
+        offt = 4ull * k.d1_two_cap * sb.tiles1_cap;
+        gsum = 4ull * k.d1_two_cap * sb.groups_cap;
+        gpre = 2 * gsum;
+        rec1 = 8ull * k.rw * sb.tile1 * sb.tiles1_cap;
+        // buckets start on whole lines, and a tile is stored in pairs of records
+        rec2 = two * 8 * k.rw * (k.len_cap + 16 * (sb.buckets_cap + 1));
+    }
+};
 
 // Byte sizes of every device buffer of a pass with key k (bb: bin_caps(k)).
 struct PassSizes {
@@ -243,14 +310,6 @@ struct PassSizes {
         tread1 = b ? 8 * bb.tiles1_cap : 0;
         tile2 = b ? sizeof(dbgk::RefChunk) * bb.chunks2_cap : 0;
     }
-};
-
-// Options of a pass besides its input: where its probe statistics go
-// (DBG_F_STATS; null: none kept) and whether keys take the test hash.
-struct PassOpts {
-    uint64_t *stats = nullptr;
-    uint32_t test_hash = 0;
-    uint32_t bin_chunks = 0, bin_div = 0, bin_shape1 = 0, bin_shape2 = 0;  // binned launch shape (0: defaults)
 };
 
 inline PassOpts opts_of(const dbg_graph *g);
@@ -293,6 +352,8 @@ struct Pass {
     // binned-mode scratch
     DevBuf bplan, bbuckets, btotals, hist1, scan1, hist2, scan2, bpartials, rec1, rec2, pstart;
     DevBuf tread1, tbucket2;
+    // sorted-tile scratch
+    DevBuf splan, stotals, sbuckets, stile2, stread, soff1, soff2, sofft, sgsum, sgpre, srec1, srec2;
     HostBuf hargs, hstatus;  // pinned: PassArgs + Instance[m_cap]; InstStatus[m_cap] + CallState
     hipEvent_t ev_a = nullptr, ev_b = nullptr, ev_c = nullptr;
     hipEvent_t marks[dbgk::kBinMarks] = {};  // binned phase boundaries (timed, uncaptured)
@@ -333,7 +394,8 @@ struct Pass {
         drop_graphs();
         DevBuf *d[] = {&packed, &ws, &partials, &tiles, &dargs, &dstatus, &bplan, &bbuckets,
                        &btotals, &hist1, &scan1, &hist2, &scan2, &bpartials, &rec1, &rec2, &pstart,
-                       &tread1, &tbucket2};
+                       &tread1, &tbucket2, &splan, &stotals, &sbuckets, &stile2, &stread, &soff1, &soff2, &sofft,
+                       &sgsum, &sgpre, &srec1, &srec2};
         for (DevBuf *b : d) b->release();
         hargs.release();
         hstatus.release();
@@ -395,6 +457,43 @@ struct Pass {
         bb.chunk2 = tbucket2.as<dbgk::RefChunk>();
         return hipSuccess;
     }
+    // Reserve the sorted-tile scratch for the key's capacities.
+    hipError_t reserve_sorted(const PassKey &k, dbgk::SortBuffers &sb) {
+        sort_caps(k, sb);
+        const SortSizes z(k, sb);
+        hipError_t e;
+        if ((e = grow(splan, z.plan)) != hipSuccess || (e = grow(stotals, z.totals)) != hipSuccess ||
+            (e = grow(sbuckets, z.buckets)) != hipSuccess || (e = grow(stile2, z.tile2_base)) != hipSuccess ||
+            (e = grow(stread, z.tile_read)) != hipSuccess || (e = grow(soff1, z.off1)) != hipSuccess ||
+            (e = grow(soff2, z.off2)) != hipSuccess || (e = grow(sofft, z.offt)) != hipSuccess ||
+            (e = grow(sgsum, z.gsum)) != hipSuccess || (e = grow(sgpre, z.gpre)) != hipSuccess ||
+            (e = grow(srec1, z.rec1)) != hipSuccess || (e = grow(srec2, z.rec2)) != hipSuccess)
+            return e;
+        sb.plan = splan.as<dbgk::SortPlan>();
+        sb.totals = stotals.as<dbgk::SortTotals>();
+        sb.buckets = sbuckets.as<dbgk::SortBucket>();
+        sb.tile2_base = stile2.as<uint64_t>();
+        sb.tile_read = stread.as<uint64_t>();
+        sb.off1 = soff1.as<uint16_t>();
+        sb.off2 = soff2.as<uint16_t>();
+        sb.offt = sofft.as<uint32_t>();
+        sb.gsum = sgsum.as<uint32_t>();
+        sb.gpre = sgpre.as<uint64_t>();
+        sb.rec1 = srec1.as<uint64_t>();
+        sb.rec2 = srec2.as<uint64_t>();
+        return hipSuccess;
+    }
+    std::vector<std::pair<PassKey, uint32_t>> sorted_memo;
+    void sorted_grids(const PassKey &k, int device, dbgk::SortBuffers &sb) {
+        for (auto &g : sorted_memo)
+            if (g.first == k) {
+                sb.grid_reduce = g.second;
+                return;
+            }
+        dbgk::sorted_grids(device, sb);
+        if (sorted_memo.size() > 16) sorted_memo.clear();
+        sorted_memo.emplace_back(k, sb.grid_reduce);
+    }
     // Grid sizes per binned key (queried once, outside any capture).
     std::vector<std::pair<PassKey, dbgk::BinBuffers>> grid_memo;
     void binned_grids(const PassKey &k, int device, dbgk::BinBuffers &bb) {
@@ -429,14 +528,15 @@ struct Pass {
         hipError_t e = hipMemcpyAsync(dargs.p, hargs.p, dbgk::kArgsBytes + sizeof(Instance) * k.m_cap,
                                       hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = dbgk::launch_prepare(da, di, dst, cs, k.m_cap, s);
-        if (e == hipSuccess) e = dbgk::launch_pack(da, packed.as<uint64_t>(), di, dst, k.len_cap, s);
+        // sorted tiles pack the reads themselves
+        if (e == hipSuccess && !k.sorted) e = dbgk::launch_pack(da, packed.as<uint64_t>(), di, dst, k.len_cap, s);
         if (e == hipSuccess)
             e = dbgk::launch_scan(da, di, dst, ws.as<uint64_t>(), partials.as<uint64_t>(),
                                   k.binned ? nullptr : tiles.as<uint64_t>(), cs, k.n_cap, s);
         return e;
     }
-    hipError_t enqueue_build(const PassKey &k, const dbgk::BinBuffers &bb, int device, hipStream_t s,
-                             bool mark = false) {
+    hipError_t enqueue_build(const PassKey &k, const dbgk::BinBuffers &bb, const dbgk::SortBuffers &sb, int device,
+                             hipStream_t s, bool mark = false) {
         dbgk::PassArgs *da = dargs.as<dbgk::PassArgs>();
         Instance *di = reinterpret_cast<Instance *>(dargs.as<unsigned char>() + dbgk::kArgsBytes);
         InstStatus *dst = dstatus.as<InstStatus>();
@@ -445,6 +545,9 @@ struct Pass {
         if (k.wide)
             e = dbgk::launch_build_wide(da, di, packed.as<uint64_t>(), ws.as<uint64_t>(), tiles.as<uint64_t>(), dst,
                                         cs, k.shape, k.stats != 0, s);
+        else if (k.sorted)
+            e = dbgk::launch_sorted(da, di, ws.as<uint64_t>(), dst, sb, k.n_cap, k.stats != 0, s,
+                                    mark ? marks : nullptr);
         else if (k.binned)
             e = dbgk::launch_binned(da, di, packed.as<uint64_t>(), ws.as<uint64_t>(), dst, bb, k.n_cap, device,
                                     k.stats != 0, s,
@@ -458,7 +561,8 @@ struct Pass {
         return e;
     }
 
-    hipError_t capture(const PassKey &k, const dbgk::BinBuffers &bb, int device, Cached &out) {
+    hipError_t capture(const PassKey &k, const dbgk::BinBuffers &bb, const dbgk::SortBuffers &sb, int device,
+                       Cached &out) {
         out.key = k;
         out.generation = generation;
         out.setup = out.build = nullptr;
@@ -466,7 +570,8 @@ struct Pass {
             hipGraph_t g = nullptr;
             hipError_t e = hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return e;
-            const hipError_t ee = half == 0 ? enqueue_setup(k, cap_stream) : enqueue_build(k, bb, device, cap_stream);
+            const hipError_t ee =
+                half == 0 ? enqueue_setup(k, cap_stream) : enqueue_build(k, bb, sb, device, cap_stream);
             e = hipStreamEndCapture(cap_stream, &g);
             if (ee != hipSuccess) e = ee;
             if (e == hipSuccess) e = hipGraphInstantiate(half == 0 ? &out.setup : &out.build, g, nullptr, nullptr, 0);
@@ -488,22 +593,22 @@ struct Pass {
                        bool time_it, hipStream_t s, const PassOpts &o, uint64_t *xkeys = nullptr,
                        uint32_t *xcounts = nullptr, uint64_t xcap = 0) {
         const Instance *hi = host_instances();
-        PassKey k = pass_key(mm, n, len, shape, binned, hi);
-        k.stats = o.stats != nullptr;
-        k.bin_chunks = o.bin_chunks;
-        k.bin_div = o.bin_div;
-        k.bin_shape1 = o.bin_shape1;
-        k.bin_shape2 = o.bin_shape2;
+        const PassKey k = pass_key(mm, n, len, shape, binned, hi, o);
         dbgk::BinBuffers bb{};
+        dbgk::SortBuffers sb{};
         if (binned) bin_caps(k, bb);
         const PassSizes z(k, bb);
         hipError_t e;
-        if ((e = grow(packed, z.packed)) != hipSuccess || (e = grow(ws, z.ws)) != hipSuccess ||
+        if ((!k.sorted && (e = grow(packed, z.packed)) != hipSuccess) || (e = grow(ws, z.ws)) != hipSuccess ||
             (e = grow(partials, z.partials)) != hipSuccess || (e = grow(dargs, z.args)) != hipSuccess ||
             (e = grow(dstatus, z.status)) != hipSuccess || (!binned && (e = grow(tiles, z.tiles)) != hipSuccess) ||
-            (binned && (e = reserve_binned(k, bb)) != hipSuccess))
+            (k.sorted && (e = reserve_sorted(k, sb)) != hipSuccess) ||
+            (binned && !k.sorted && (e = reserve_binned(k, bb)) != hipSuccess))
             return e;
-        if (binned) {
+        if (k.sorted) {
+            sorted_grids(k, device, sb);
+            shapes = dbgk::auto_shapes(k.rw, k.d1_cap);
+        } else if (binned) {
             binned_grids(k, device, bb);
             shapes = (bb.shape1 + 1) | (bb.shape2 + 1) << 8;
         }
@@ -516,7 +621,7 @@ struct Pass {
             if (!c) {
                 if (graphs.size() >= 8 || (!graphs.empty() && graphs[0].generation != generation)) drop_graphs();
                 Cached fresh{};
-                e = capture(k, bb, device, fresh);
+                e = capture(k, bb, sb, device, fresh);
                 if (e != hipSuccess) {
                     if (fresh.setup) (void)hipGraphExecDestroy(fresh.setup);
                     if (fresh.build) (void)hipGraphExecDestroy(fresh.build);
@@ -532,7 +637,7 @@ struct Pass {
         e = c ? hipGraphLaunch(c->setup, s) : enqueue_setup(k, s);
         if (time_it && e == hipSuccess) (void)hipEventRecord(ev_b, s);
         marked = !c && time_it && binned;
-        if (e == hipSuccess) e = c ? hipGraphLaunch(c->build, s) : enqueue_build(k, bb, device, s, marked);
+        if (e == hipSuccess) e = c ? hipGraphLaunch(c->build, s) : enqueue_build(k, bb, sb, device, s, marked);
         if (time_it && e == hipSuccess) (void)hipEventRecord(ev_c, s);
         if (e != hipSuccess) return e;
         m = mm;
@@ -641,11 +746,14 @@ inline PassOpts opts_of(const dbg_graph *g) {
 // Segment geometry of a binned table of at least `cap` slots: d1 level-1
 // buckets of `fan` segments each (about the square root, so both partition
 // passes write runs of similar length), d1 * fan segments of kSegSlots slots
-// in all (a segment is a pair of digits of the key image).  False if the
-// table is too large for the two levels.
-inline bool binned_geometry(uint64_t cap, uint32_t *d1, uint32_t *fan, uint64_t *parts) {
+// in all (a segment is a pair of digits of the key image).  A table of up to
+// `single` segments has one level: a bucket per segment.  False if the table
+// is too large for the two levels.
+inline bool binned_geometry(uint64_t cap, uint32_t *d1, uint32_t *fan, uint64_t *parts,
+                            uint64_t single = dbgk::kSingleParts) {
     const uint64_t want = std::max<uint64_t>(1, (cap + dbgk::kSegSlots - 1) / dbgk::kSegSlots);
     uint64_t target = (uint64_t)std::ceil(std::sqrt((double)want));
+    if (want <= single) target = want;
     target = std::max<uint64_t>(1, std::min<uint64_t>(target, dbgk::kMaxD1));
     const uint64_t f = (want + target - 1) / target;
     if (f > dbgk::kMaxFan) return false;
@@ -682,7 +790,9 @@ inline hipError_t order_after_zero(dbg_graph *g, hipStream_t s) {
 inline hipError_t allocate_table(dbg_graph *g, uint64_t cap) {
     if (g->binned) {
         uint64_t parts = 0;
-        if (!binned_geometry(cap, &g->d1, &g->fan, &parts)) return hipErrorInvalidValue;
+        // one level only where the partition takes it: the shaped scatters are tuned to two
+        const uint64_t single = g->bin_shape1 || g->bin_shape2 ? 0 : dbgk::kSingleParts;
+        if (!binned_geometry(cap, &g->d1, &g->fan, &parts, single)) return hipErrorInvalidValue;
         g->parts = (uint32_t)parts;
         cap = parts * dbgk::kSegSlots;
         hipError_t e;

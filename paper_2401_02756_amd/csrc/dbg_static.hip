@@ -89,31 +89,58 @@ extern "C" int dbg_build_device_static(dbg_graph *g, const uint8_t *d_reads, uin
     Instance hi[1];
     fill_instance(hi[0], g, 0, n_reads, k);
     if (!binned) hi[0].parts = hi[0].d1 = hi[0].fan = 0;
-    const PassKey key = pass_key(1, n_reads, reads_len, g->shape, binned, hi);
+    PassOpts o = opts_of(g);
+    o.stats = nullptr;  // the statistics kernels are not part of this entry point
+    const PassKey key = pass_key(1, n_reads, reads_len, g->shape, binned, hi, o);
     dbgk::BinBuffers bb{};
+    dbgk::SortBuffers sb{};
     if (binned) bin_caps(key, bb);
     const PassSizes z(key, bb);
+    // What a pass is refused by: two levels of histograms and scattered
+    // records, which is what the array was sized for.  Sorted tiles need less.
+    Instance two = hi[0];
+    if (binned) {
+        uint64_t parts = 0;
+        if (!binned_geometry(g->cap, &two.d1, &two.fan, &parts, 0)) return DBG_E_SCRATCH;
+        two.parts = (uint32_t)parts;
+    }
+    PassOpts shaped = o;
+    if (key.sorted) shaped.bin_shape1 = shaped.bin_shape2 = 3;
+    const PassKey key2 = key.sorted ? pass_key(1, n_reads, reads_len, g->shape, binned, &two, shaped) : key;
+    dbgk::BinBuffers bb2{};
+    if (binned) bin_caps(key2, bb2);
+    const PassSizes z2(key2, bb2);
     Carve c;
-    const uint64_t o_packed = c.take(z.packed), o_ws = c.take(z.ws), o_partials = c.take(z.partials),
-                   o_args = c.take(z.args), o_status = c.take(z.status), o_tiles = c.take(z.tiles);
+    const uint64_t o_packed = c.take(z2.packed), o_ws = c.take(z2.ws), o_partials = c.take(z2.partials),
+                   o_args = c.take(z2.args), o_status = c.take(z2.status), o_tiles = c.take(z2.tiles);
     uint64_t o_plan = 0, o_buckets = 0, o_totals = 0, o_hist1 = 0, o_scan1 = 0, o_hist2 = 0, o_scan2 = 0,
              o_bpart = 0, o_rec1 = 0, o_rec2 = 0, o_pstart = 0, o_tread1 = 0, o_tile2 = 0;
     if (binned) {
-        o_plan = c.take(z.plan);
-        o_buckets = c.take(z.buckets);
-        o_totals = c.take(z.totals);
-        o_hist1 = c.take(z.hist1);
-        o_scan1 = c.take(z.scan1);
-        o_hist2 = c.take(z.hist2);
-        o_scan2 = c.take(z.scan2);
-        o_bpart = c.take(z.bpartials);
-        o_rec1 = c.take(z.rec1);
-        o_rec2 = c.take(z.rec2);
-        o_pstart = c.take(z.pstart);
-        o_tread1 = c.take(z.tread1);
-        o_tile2 = c.take(z.tile2);
+        o_plan = c.take(z2.plan);
+        o_buckets = c.take(z2.buckets);
+        o_totals = c.take(z2.totals);
+        o_hist1 = c.take(z2.hist1);
+        o_scan1 = c.take(z2.scan1);
+        o_hist2 = c.take(z2.hist2);
+        o_scan2 = c.take(z2.scan2);
+        o_bpart = c.take(z2.bpartials);
+        o_rec1 = c.take(z2.rec1);
+        o_rec2 = c.take(z2.rec2);
+        o_pstart = c.take(z2.pstart);
+        o_tread1 = c.take(z2.tread1);
+        o_tile2 = c.take(z2.tile2);
     }
     if (c.used > kStaticScratchBytes) return DBG_E_SCRATCH;
+    uint64_t so[12] = {};  // the sorted tiles' buffers lie behind the common ones
+    if (key.sorted) {
+        sort_caps(key, sb);
+        const SortSizes sz(key, sb);
+        const uint64_t want[12] = {sz.plan, sz.totals, sz.buckets, sz.tile2_base, sz.tile_read, sz.off1,
+                                   sz.off2, sz.offt,   sz.gsum,    sz.gpre,       sz.rec1,      sz.rec2};
+        c.used = o_tiles;
+        for (int i = 0; i < 12; ++i) so[i] = c.take(want[i]);
+        if (c.used > kStaticScratchBytes) return DBG_E_SCRATCH;
+    }
 
     rc = settle_mode(g, k);  // k <= 32 here: at most a switch to the direct build, no allocation
     if (rc != DBG_OK) return rc;
@@ -128,7 +155,21 @@ extern "C" int dbg_build_device_static(dbg_graph *g, const uint8_t *d_reads, uin
     auto *cs = reinterpret_cast<CallState *>(dst + key.m_cap);
     auto *packed = reinterpret_cast<uint64_t *>(base + o_packed);
     auto *ws = reinterpret_cast<uint64_t *>(base + o_ws);
-    if (binned) {
+    if (key.sorted) {
+        sb.plan = reinterpret_cast<dbgk::SortPlan *>(base + so[0]);
+        sb.totals = reinterpret_cast<dbgk::SortTotals *>(base + so[1]);
+        sb.buckets = reinterpret_cast<dbgk::SortBucket *>(base + so[2]);
+        sb.tile2_base = reinterpret_cast<uint64_t *>(base + so[3]);
+        sb.tile_read = reinterpret_cast<uint64_t *>(base + so[4]);
+        sb.off1 = reinterpret_cast<uint16_t *>(base + so[5]);
+        sb.off2 = reinterpret_cast<uint16_t *>(base + so[6]);
+        sb.offt = reinterpret_cast<uint32_t *>(base + so[7]);
+        sb.gsum = reinterpret_cast<uint32_t *>(base + so[8]);
+        sb.gpre = reinterpret_cast<uint64_t *>(base + so[9]);
+        sb.rec1 = reinterpret_cast<uint64_t *>(base + so[10]);
+        sb.rec2 = reinterpret_cast<uint64_t *>(base + so[11]);
+        dbgk::sorted_grids(g->device, sb);
+    } else if (binned) {
         bb.plan = reinterpret_cast<dbgk::BinPlan *>(base + o_plan);
         bb.buckets = reinterpret_cast<dbgk::Bucket *>(base + o_buckets);
         bb.totals = reinterpret_cast<dbgk::BinTotals *>(base + o_totals);
@@ -149,19 +190,19 @@ extern "C" int dbg_build_device_static(dbg_graph *g, const uint8_t *d_reads, uin
         dbgk::binned_grids(g->device, bb);
     }
     dbgk::PassArgs a;
-    PassOpts o = opts_of(g);
-    o.stats = nullptr;  // the statistics kernels are not part of this entry point
     fill_args(a, key, z, 1, hi, d_reads, reads_len, d_offsets, n_reads, true, nullptr, nullptr, 0, o);
 
     hipLaunchKernelGGL(k_put_args, dim3(1), dim3(64), 0, s, a, hi[0], dargs);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = dbgk::launch_prepare(da, di, dst, cs, key.m_cap, s);
-    if (e == hipSuccess) e = dbgk::launch_pack(da, packed, di, dst, key.len_cap, s);
+    if (e == hipSuccess && !key.sorted) e = dbgk::launch_pack(da, packed, di, dst, key.len_cap, s);
     if (e == hipSuccess)
         e = dbgk::launch_scan(da, di, dst, ws, reinterpret_cast<uint64_t *>(base + o_partials),
                               binned ? nullptr : reinterpret_cast<uint64_t *>(base + o_tiles), cs, key.n_cap, s);
     if (e == hipSuccess) {
-        if (binned)
+        if (key.sorted)
+            e = dbgk::launch_sorted(da, di, ws, dst, sb, key.n_cap, false, s, nullptr);
+        else if (binned)
             e = dbgk::launch_binned(da, di, packed, ws, dst, bb, key.n_cap, g->device, false, s, nullptr);
         else
             e = dbgk::launch_build(da, di, packed, ws, reinterpret_cast<uint64_t *>(base + o_tiles), dst, cs,
