@@ -50,13 +50,17 @@ __device__ __forceinline__ void atomic_add_u64(uint64_t *p, uint64_t v) {
 }
 
 // Instance owning a global read index: the last i with read_begin <= r.
-__device__ __forceinline__ uint32_t instance_of_read(const Instance *inst, uint32_t m, uint64_t r) {
-    uint32_t lo = 0, hi = m;
+// The instance of read r, one of [lo, hi).
+__device__ __forceinline__ uint32_t instance_of_read(const Instance *inst, uint32_t lo, uint32_t hi, uint64_t r) {
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;
         if (inst[mid].read_begin <= r) lo = mid; else hi = mid;
     }
     return lo;
+}
+
+__device__ __forceinline__ uint32_t instance_of_read(const Instance *inst, uint32_t m, uint64_t r) {
+    return instance_of_read(inst, 0, m, r);
 }
 
 __device__ __forceinline__ uint32_t instance_of_byte(const Instance *inst, uint32_t m, uint64_t b) {

@@ -3,10 +3,11 @@
 // One build pass over a batch of m graphs ("instances"; a plain build is the
 // case m = 1) runs these kernels in stream order:
 //
-//   prepare    -- zero the per-call status words and the work cursor
+//   begin      -- the argument block from pinned host memory; zero the
+//                 per-call status words, the cursors
 //   pack       -- ASCII -> 2-bit letter codes, 32 bases per uint64, first
 //                 base in the top bits; flags bytes outside ACGTacgt
-//   scan_*     -- windows per read, exclusive prefix over reads, and the
+//   scan       -- windows per read, exclusive prefix over reads, and the
 //                 tile -> first-read map the build kernel starts from
 //   build      -- persistent: workgroups pull tiles of windows from a
 //                 cursor, extract each window's (k-1)-mer and next letter,
@@ -76,15 +77,16 @@ struct PassArgs {
     uint64_t n_reads;
     uint64_t reads_len;     // bytes (off[n] - off[0] when valid)
     uint64_t max_windows;   // more windows than this flags every instance invalid
-    uint64_t tile_cap;      // direct build: tile map entries
+    uint64_t tile_cap;      // tile map entries
     uint64_t parts_total;   // binned build: segments over all instances
     uint64_t *xkeys;        // binned build of one instance: when set, the reduce also writes
     uint32_t *xcounts;      // every vertex of the graph to these arrays (keys of one or two
     uint64_t xcap;          // words, four counters each; entries past xcap are dropped)
     uint64_t *stats;        // probe statistics of this pass (kStat* words), accumulated; null: not kept
+    struct InstStatus *host_status;  // pinned host memory that the pass's last kernel stores the statuses to, or null
     uint32_t m;             // instances
     uint32_t check_ends;    // require off[n] - off[0] == reads_len
-    uint32_t tile;          // direct build: windows per tile
+    uint32_t tile;          // windows per tile of the tile map
     uint32_t test_hash;     // nonzero: every key's home slot is its low 3 bits (tests only)
 };
 constexpr uint32_t kArgsBytes = 128;
@@ -200,6 +202,9 @@ struct RefChunk {       // per pass-2 chunk: everything its kernels need, in one
     uint32_t d1;              // level-1 buckets of the instance (first digit's radix)
 };
 
+struct SortPlan;
+struct SortTotals;
+
 struct BinTotals {
     uint64_t tiles1, chunk1, chunks1, hist1_len, buckets, chunk2, chunks2, hist2_len, records;
 };
@@ -277,6 +282,7 @@ struct SortBuffers {    // device scratch of one pass
     uint32_t *gsum;           // group sums (d1_max x groups_cap)
     uint64_t *gpre;           // and what lies before each group
     uint64_t *rec1, *rec2;    // sorted tiles of records
+    uint64_t *done;           // kDoneWords, zeroed: workgroups of the last kernel that are through
     uint64_t tiles1_cap, tiles2_cap, groups_cap, buckets_cap, parts_cap;
     uint32_t d1_max, fan_max, row1, row2;
     uint32_t tile1, tile2;    // records of a tile
@@ -284,6 +290,11 @@ struct SortBuffers {    // device scratch of one pass
     uint32_t two_level;       // some instance needs the second level
     uint32_t grid_reduce;     // persistent grid (sorted_grids)
 };
+
+// One address takes about 30 ns for each atomic that wants its old value, so the
+// workgroups count themselves on kDoneLines lines and the last of each line on
+// one more.
+constexpr uint32_t kDoneLines = 32, kDoneStride = 16, kDoneWords = (kDoneLines + 1) * kDoneStride;
 
 // The scatter shapes that dbg_stats reports for automatic shapes (code of the
 // first | second << 8): big tiles, of 128 KB in a first level of many buckets;
@@ -296,33 +307,41 @@ constexpr uint32_t auto_shapes(uint32_t rec_words, uint32_t d1) {
 // while a launch is being captured).
 void sorted_grids(int device, SortBuffers &sb);
 hipError_t launch_sorted(const PassArgs *args, const Instance *inst, const uint64_t *ws, InstStatus *st,
-                         const SortBuffers &sb, uint64_t n_cap, bool stats, hipStream_t s, hipEvent_t *marks);
+                         const SortBuffers &sb, uint64_t n_cap, bool single, bool stats, hipStream_t s,
+                         hipEvent_t *marks);
 
 // Fill the grid sizes of bb from occupancy and its capacities.
 void binned_grids(int device, BinBuffers &bb);
 
-constexpr uint32_t kScanBlock = 256;
-constexpr uint32_t kScanPerThread = 4;
+constexpr uint32_t kScanBlock = 1024;
+constexpr uint32_t kScanPerThread = 8;
 constexpr uint32_t kScanReads = kScanBlock * kScanPerThread;  // reads per scan block
 constexpr uint32_t kMapReads = 256;  // reads of one tile staged in LDS
 
 __host__ __device__ inline uint64_t packed_words(uint64_t bytes) { return (bytes + 31) / 32 + 2; }
 inline uint64_t scan_blocks(uint64_t n_reads) { return (n_reads + kScanReads - 1) / kScanReads; }
+// Words of the scan's sums (two per block).
+inline uint64_t scan_words(uint64_t n_reads) { return 2 * scan_blocks(n_reads); }
 inline uint64_t max_tiles(uint64_t bytes, uint64_t tile) { return bytes / tile + 2; }
 
 // Launchers (all stream-ordered; they only enqueue).  `args` and `inst` are
 // device pointers; *_cap values are host upper bounds that size grids.
-hipError_t launch_prepare(const PassArgs *args, Instance *inst, InstStatus *st, CallState *cs,
-                          uint32_t m_cap, hipStream_t s);
+// host: the argument block and instances in pinned host memory (null: they are
+// in args and inst already).  done: kDoneWords to clear (may be null).
+hipError_t launch_begin(const void *host, PassArgs *args, Instance *inst, InstStatus *st, CallState *cs,
+                        uint64_t *done, uint32_t m_cap, hipStream_t s);
 hipError_t launch_fill_zero(uint64_t *words, uint64_t n_words, hipStream_t s);
 // out[i] = src[idx[i]] for i < n (device arrays).
 hipError_t launch_gather_u64(const uint64_t *src, const uint64_t *idx, uint64_t n, uint64_t *out, hipStream_t s);
 hipError_t launch_pack(const PassArgs *args, uint64_t *packed, const Instance *inst, InstStatus *st,
                        uint64_t len_cap, hipStream_t s);
-// tile_read may be null (no tile map).
+// sums: scan_words words.  tile_read may be
+// null (no tile map).  plan, tot: the sorted-tile plan of a one-instance pass
+// (null otherwise); the scan then also checks the bytes of reads without a
+// window, which no tile covers.
 hipError_t launch_scan(const PassArgs *args, const Instance *inst, InstStatus *st, uint64_t *ws,
-                       uint64_t *partials, uint64_t *tile_read, CallState *cs, uint64_t n_cap,
-                       hipStream_t s);
+                       uint64_t *sums, uint64_t *tile_read, CallState *cs, SortPlan *plan, SortTotals *tot,
+                       uint64_t n_cap, hipStream_t s);
 // stats: launch the kernels that keep probe statistics (PassArgs::stats set).
 hipError_t launch_build(const PassArgs *args, const Instance *inst, const uint64_t *packed,
                         const uint64_t *ws, const uint64_t *tile_read, InstStatus *st, CallState *cs,

@@ -25,33 +25,46 @@
 
 namespace dbgk {
 namespace {
-// ---------------------------------------------------------------- prepare
+// ---------------------------------------------------------------- begin
 
-__global__ void k_prepare(const PassArgs *__restrict__ args, Instance *inst, InstStatus *st,
-                          CallState *cs) {
-    const uint32_t m = args->m;
-    const uint64_t n = args->n_reads;
-    const uint64_t *off = as_global(args->off);
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < m) {
-        st[i].err = inst[i].skip ? kErrSkip : 0u;
-        st[i].pad = 0;
-        st[i].claimed = 0;
-        st[i].inserts = 0;
-        st[i].windows = 0;
-        st[i].emitted = 0;
-        // byte range of the instance, relative to the first read's first byte
-        if (n) {
-            const uint64_t off0 = off[0];
-            const uint64_t rb = min(inst[i].read_begin, n), re = min(inst[i].read_end, n);
-            inst[i].byte_begin = off[rb] - off0;
-            inst[i].byte_end = off[re] - off0;
+// The pass's argument block and instances, from pinned host memory (read once
+// over the link: a copy command and this kernel's own launch take longer than
+// the few hundred bytes do), its statuses and cursors, and the counters of its end.
+constexpr uint32_t kInstWords = sizeof(Instance) / 8;
+static_assert(sizeof(Instance) % 8 == 0, "copied in words");
+
+__global__ void k_begin(const uint64_t *host, PassArgs *args, Instance *inst, InstStatus *st, CallState *cs,
+                        uint64_t *done, uint32_t n_done) {
+    const uint32_t x = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    for (uint32_t i = x; i < n_done; i += stride) done[i] = 0;
+    const PassArgs *a = host ? reinterpret_cast<const PassArgs *>(host) : args;
+    const Instance *in = host ? reinterpret_cast<const Instance *>(host + kArgsBytes / 8) : inst;
+    const uint32_t m = a->m;
+    const uint64_t n = a->n_reads;
+    const uint64_t *off = as_global(a->off);
+    if (host) {
+        if (x < sizeof(PassArgs) / 8) reinterpret_cast<uint64_t *>(args)[x] = host[x];
+        for (uint32_t w = x; w < m * kInstWords; w += stride) {
+            const uint32_t f = w % kInstWords;
+            if (f == offsetof(Instance, byte_begin) / 8 || f == offsetof(Instance, byte_end) / 8) continue;
+            reinterpret_cast<uint64_t *>(inst)[w] = host[kArgsBytes / 8 + w];
         }
     }
-    if (i == 0) {
-        cs->cursor = 0;
-        cs->windows = 0;
+    for (uint32_t i = x; i < m; i += stride) {
+        InstStatus s{};
+        s.err = in[i].skip ? kErrSkip : 0u;
+        st[i] = s;
+        // byte range of the instance, relative to the first read's first byte
+        uint64_t b0 = 0, b1 = 0;
+        if (n) {
+            const uint64_t off0 = off[0];
+            b0 = off[min(in[i].read_begin, n)] - off0;
+            b1 = off[min(in[i].read_end, n)] - off0;
+        }
+        inst[i].byte_begin = b0;
+        inst[i].byte_end = b1;
     }
+    if (x == 0) *cs = CallState{};
 }
 
 __global__ void k_fill_zero(uint64_t *__restrict__ words, uint64_t n_words) {
@@ -124,11 +137,10 @@ struct ReadCount {
     bool bad;
 };
 
-__device__ __forceinline__ ReadCount count_read(const uint64_t *off, uint64_t off0, uint64_t r,
-                                                uint64_t n, uint64_t len, bool check_ends,
-                                                uint32_t k) {
+// Read r lies at [a, b).
+__device__ __forceinline__ ReadCount count_read(uint64_t a, uint64_t b, uint64_t off0, uint64_t r, uint64_t n,
+                                                uint64_t len, bool check_ends, uint32_t k) {
     ReadCount rc{0, 0, false};
-    const uint64_t a = off[r], b = off[r + 1];
     if (b < a || a < off0 || b - off0 > len) {
         rc.bad = true;
         return rc;
@@ -142,140 +154,189 @@ __device__ __forceinline__ ReadCount count_read(const uint64_t *off, uint64_t of
     return rc;
 }
 
-// Per-read windows, block-local exclusive prefix and block totals; also the
-// k-mers and windows of each instance.  A single instance's totals are summed
-// from per-block partials (kpart) by k_scan_partials: an atomic per block on
-// one address would serialise about a thousand times.  In a batch, a block
-// whose reads all belong to one instance, as they almost always do, adds its
-// totals with one atomic.
-__global__ __launch_bounds__(kScanBlock) void k_scan_local(
+// Offsets that overlap can sum to anything: a block's sum stops here, above any
+// valid total and low enough for the sum of all blocks not to wrap.
+constexpr uint64_t kMostOfBlock = 1ull << 40;
+
+// Sum of v over the block's threads.
+__device__ __forceinline__ uint64_t block_sum(uint64_t v, uint64_t *s_wave) {
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+    if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = 0;
+    for (uint32_t i = 0; i < kScanBlock / 64; ++i) v += s_wave[i];
+    __syncthreads();
+    return v;
+}
+
+// Windows per read and their exclusive prefix, the first read of every tile,
+// the k-mers and windows of each instance, and the plan of a one-instance pass
+// by sorted tiles.  One launch counts (a pair of sums per block of 8192 reads),
+// a second scans, each block adding up the sums before its own; reads that fit
+// one block take a single launch that does both.
+// In a batch, a wavefront whose reads all belong to one instance, as they almost
+// always do, adds its totals to it with one atomic.  Valid offsets give at most
+// one window per byte, which is what the buffers are sized for; overlapping
+// (malformed) offsets can exceed that, and then every instance is flagged
+// invalid and no window is processed.
+// Bound by latency: a lane's loads are issued together, a row of 64 reads at a
+// time.  20 us for 0.93 million reads and 61 for 2.2 million of which one in ten
+// has no window (count, map and tile map were four launches of 57 and 73 us with
+// their gaps).  A single launch over all blocks that hands out tickets and looks
+// back at the blocks before took 19 and 57 us, but 158 against 89 for a batch of
+// 48 sets: each ticket and each look at a watched line takes its turn.
+template <bool COUNT, bool WRITE>
+__global__ __launch_bounds__(kScanBlock) void k_scan(
     const PassArgs *__restrict__ args, const Instance *__restrict__ inst, InstStatus *st,
-    uint64_t *__restrict__ ws, uint64_t *__restrict__ partials, uint64_t *__restrict__ kpart) {
-    __shared__ uint32_t s_t0, s_t1;
+    uint64_t *__restrict__ ws, uint64_t *sums, uint64_t *__restrict__ tile_read, CallState *cs,
+    SortPlan *__restrict__ plan, SortTotals *__restrict__ tot) {
+    __shared__ uint64_t s_wave[kScanBlock / 64];
     const uint64_t *__restrict__ off = as_global(args->off);
-    const uint64_t n = args->n_reads, len = args->reads_len;
-    const uint32_t m = args->m, check_ends = args->check_ends;
-    const uint64_t rb = (uint64_t)blockIdx.x * kScanReads;
-    if (rb >= n) {  // grid sized for the capacity: blocks past the reads add nothing
-        if (threadIdx.x == 0) partials[blockIdx.x] = kpart[blockIdx.x] = 0;
+    const uint8_t *__restrict__ ascii = as_global(args->reads);
+    const uint64_t n = args->n_reads, len = args->reads_len, tile_cap = args->tile_cap;
+    const uint32_t m = args->m, check_ends = args->check_ends, tile = args->tile;
+    const uint64_t block = blockIdx.x, rb = block * kScanReads;
+    if (rb >= n) {  // grid sized for the capacity
+        if (WRITE && n == 0 && block == 0 && threadIdx.x == 0 && plan) {
+            *plan = SortPlan{};
+            *tot = SortTotals{};
+        }
         return;
     }
+    const bool last_block = rb + kScanReads >= n, single = m == 1;
     const uint64_t off0 = off[0];
-    const uint64_t r0 = rb + (uint64_t)threadIdx.x * kScanPerThread;
-    if (threadIdx.x == 0) {
-        s_t0 = m == 1 ? 0u : instance_of_read(inst, m, rb);
-        s_t1 = m == 1 ? 0u : instance_of_read(inst, m, min(rb + kScanReads, n) - 1);
-    }
-    __syncthreads();
-    const bool uniform = s_t0 == s_t1;
-    uint64_t w[kScanPerThread];
-    uint64_t tw = 0, tk = 0;
-    uint32_t t = (m == 1 || r0 >= n) ? 0u : instance_of_read(inst, m, r0);
-    uint64_t run_w = 0, run_k = 0;  // this thread's sums for instance t (non-uniform blocks)
+    // A wavefront has 64 * kScanPerThread reads, a lane every 64th of them.
+    const uint64_t first = rb + (uint64_t)(threadIdx.x & ~63u) * kScanPerThread, r0 = first + (threadIdx.x & 63);
+    uint64_t at[kScanPerThread], to[kScanPerThread];  // where the reads lie: all loads first
 #pragma unroll
     for (uint32_t i = 0; i < kScanPerThread; ++i) {
-        const uint64_t r = r0 + i;
-        w[i] = 0;
-        if (r < n) {
-            while (t + 1 < m && inst[t + 1].read_begin <= r) {
-                if (!uniform && (run_w | run_k)) {
-                    atomic_add_u64(&st[t].windows, run_w);
-                    atomic_add_u64(&st[t].inserts, run_k);
-                }
-                run_w = run_k = 0;
-                ++t;
-            }
-            const ReadCount rc = count_read(off, off0, r, n, len, check_ends != 0, inst[t].k);
-            if (rc.bad) atomic_or_u32(&st[t].err, kErrInval);
-            w[i] = rc.windows;
-            tw += rc.windows;
-            tk += rc.kmers;
-            run_w += rc.windows;
-            run_k += rc.kmers;
-        }
+        at[i] = off[min(r0 + 64 * i, n - 1)];
+        to[i] = off[min(r0 + 64 * i, n - 1) + 1];
     }
-    if (!uniform && (run_w | run_k)) {
-        atomic_add_u64(&st[t].windows, run_w);
-        atomic_add_u64(&st[t].inserts, run_k);
+    uint64_t before = 0, kbefore = 0;  // the blocks before
+    if (WRITE && !COUNT) {
+        for (uint64_t i = threadIdx.x; i < block; i += kScanBlock) {
+            before += sums[2 * i];
+            if (last_block) kbefore += sums[2 * i + 1];
+        }
+        before = block_sum(before, s_wave);
+        if (last_block) kbefore = block_sum(kbefore, s_wave);
+    }
+    const uint32_t t0 = single ? 0u : instance_of_read(inst, m, min(first, n - 1));
+    const bool uniform = single || t0 + 1 == m || inst[t0 + 1].read_begin >= min(first + 64 * kScanPerThread, n);
+    const uint32_t t1 = uniform ? t0 : instance_of_read(inst, m, min(first + 64 * kScanPerThread, n) - 1);
+    const uint32_t k0 = inst[t0].k;
+    uint64_t w[kScanPerThread];
+    uint64_t tw = 0, tk = 0;
+    uint32_t bad = 0, bare = 0;  // bit i: this read's offsets are bad, it has no window
+#pragma unroll
+    for (uint32_t i = 0; i < kScanPerThread; ++i) {
+        const uint64_t r = r0 + 64 * i;
+        const uint32_t k = uniform ? k0 : inst[instance_of_read(inst, t0, t1 + 1, min(r, n - 1))].k;
+        const ReadCount rc = count_read(at[i], to[i], off0, r, n, len, check_ends != 0, k);
+        const bool in = r < n;
+        w[i] = in ? rc.windows : 0;
+        const uint64_t kmers = in ? rc.kmers : 0;
+        tw += w[i];
+        tk += kmers;
+        if (!COUNT) continue;
+        bad |= in && rc.bad ? 1u << i : 0u;
+        bare |= in && !rc.bad && !rc.windows ? 1u << i : 0u;
+    }
+    if (COUNT) {
+        if (bad)
+            for (uint32_t i = 0; i < kScanPerThread; ++i)
+                if (bad >> i & 1) atomic_or_u32(&st[single ? 0u : instance_of_read(inst, m, r0 + 64 * i)].err, kErrInval);
+        if (plan && bare)  // no tile covers these
+            for (uint32_t i = 0; i < kScanPerThread; ++i)
+                if (bare >> i & 1) {
+                    bool good = true;
+                    const uint64_t q0 = off[r0 + 64 * i] - off0, q1 = off[r0 + 64 * i + 1] - off0;
+                    for (uint64_t q = q0; q < q1; q += 16)
+#pragma unroll
+                        for (uint32_t j = 0; j < 16; ++j) good &= valid_letter(ascii[min(q + j, q1 - 1)]);
+                    if (!good) atomic_or_u32(&st[0].err, kErrBase);
+                }
+        if (!single && uniform) {
+            uint64_t sw = tw, sk = tk;
+            for (int d = 32; d >= 1; d >>= 1) {
+                sw += __shfl_xor(sw, d, 64);
+                sk += __shfl_xor(sk, d, 64);
+            }
+            if ((threadIdx.x & 63) == 0 && sw) {
+                atomic_add_u64(&st[t0].windows, sw);
+                atomic_add_u64(&st[t0].inserts, sk);
+            }
+        }
+        if (!uniform)  // the last lane of each instance in a row adds what the row has of it
+            for (uint32_t i = 0; i < kScanPerThread; ++i) {
+                const uint64_t r = r0 + 64 * i;
+                const uint32_t t = r < n ? instance_of_read(inst, t0, t1 + 1, r) : m, lane = threadIdx.x & 63;
+                ReadCount rc{0, 0, false};
+                if (r < n) rc = count_read(off[r], off[r + 1], off0, r, n, len, check_ends != 0, inst[t].k);
+                const uint64_t sw = wave_inclusive_scan(rc.windows), sk = wave_inclusive_scan(rc.kmers);
+                const uint32_t next = __shfl_down(t, 1, 64);
+                const uint64_t ends = __ballot(lane == 63 || next != t), lower = ends & ((1ull << lane) - 1);
+                const int prev = lower ? 63 - __builtin_clzll(lower) : 0;
+                const uint64_t pw = __shfl(sw, prev, 64), pk = __shfl(sk, prev, 64);
+                if ((ends >> lane & 1) && t < m) {
+                    atomic_add_u64(&st[t].windows, sw - (lower ? pw : 0));
+                    atomic_add_u64(&st[t].inserts, sk - (lower ? pk : 0));
+                }
+            }
+        if (WRITE && bad) __threadfence();  // the plan looks at the error bits
+    }
+    if (!WRITE) {
+        const uint64_t total = min(block_sum(tw, s_wave), kMostOfBlock), ktotal = min(block_sum(tk, s_wave), kMostOfBlock);
+        if (threadIdx.x == 0) {
+            sums[2 * block] = total;
+            sums[2 * block + 1] = ktotal;
+        }
+        return;
     }
     uint64_t total;
     uint64_t pre = block_exclusive_scan(tw, &total);
+    pre = __shfl(pre, 0, 64) + before;  // before this wavefront's reads
+    const bool narrow = !__any(tw >> 26);  // a row's sums fit 32 bits
+    const uint32_t shift = tile & (tile - 1) ? 0u : (uint32_t)__builtin_ctz(tile);
 #pragma unroll
     for (uint32_t i = 0; i < kScanPerThread; ++i) {
-        const uint64_t r = r0 + i;
-        if (r < n) ws[r] = pre;
-        pre += w[i];
-    }
-    if (threadIdx.x == 0) partials[blockIdx.x] = total;
-    uint64_t ktotal = 0;
-    if (uniform) block_exclusive_scan(tk, &ktotal);
-    if (threadIdx.x == 0) {
-        kpart[blockIdx.x] = m == 1 ? ktotal : 0;
-        if (m > 1 && uniform && (total | ktotal)) {
-            atomic_add_u64(&st[s_t0].inserts, ktotal);
-            atomic_add_u64(&st[s_t0].windows, total);
-        }
-    }
-}
-
-// Exclusive scan of the block totals.  Valid offsets give at most one window
-// per byte, which is what the tile map is sized for; overlapping (malformed)
-// offsets can exceed that, and then every instance is flagged invalid and no
-// window is processed.
-__global__ __launch_bounds__(1024) void k_scan_partials(const PassArgs *__restrict__ args,
-                                                       uint64_t *partials, const uint64_t *kpart, uint64_t nb,
-                                                       CallState *cs, InstStatus *st) {
-    const uint64_t max_windows = args->max_windows;
-    const uint32_t m = args->m;
-    uint64_t carry = 0, kcarry = 0;
-    for (uint64_t base = 0; base < nb; base += blockDim.x) {
-        const uint64_t i = base + threadIdx.x;
-        const uint64_t v = i < nb ? partials[i] : 0;
-        uint64_t total, ktotal = 0;
-        const uint64_t ex = block_exclusive_scan(v, &total);
-        if (i < nb) partials[i] = carry + ex;
-        carry += total;
-        if (m == 1) {
-            block_exclusive_scan(i < nb ? kpart[i] : 0, &ktotal);
-            kcarry += ktotal;
-        }
-    }
-    if (m == 1 && threadIdx.x == 0) {  // the single instance's totals
-        st[0].windows = carry;
-        st[0].inserts = kcarry;
-    }
-    if (carry > max_windows) {
-        for (uint32_t i = threadIdx.x; i < m; i += blockDim.x) atomic_or_u32(&st[i].err, kErrInval);
-        carry = 0;
-    }
-    if (threadIdx.x == 0) cs->windows = carry;
-}
-
-__global__ __launch_bounds__(kScanBlock) void k_scan_add(
-    const PassArgs *__restrict__ args, const Instance *__restrict__ inst, uint64_t *__restrict__ ws,
-    const uint64_t *__restrict__ partials, uint64_t *__restrict__ tile_read) {
-    const uint64_t *__restrict__ off = as_global(args->off);
-    const uint64_t n = args->n_reads, len = args->reads_len, tile_cap = args->tile_cap;
-    const uint32_t m = args->m, check_ends = args->check_ends, tile = args->tile;
-    if ((uint64_t)blockIdx.x * kScanReads >= n) return;
-    const uint64_t r0 = (uint64_t)blockIdx.x * kScanReads + (uint64_t)threadIdx.x * kScanPerThread;
-    const uint64_t add = partials[blockIdx.x];
-    const uint64_t off0 = off[0];
-    uint32_t t = (m == 1 || r0 >= n) ? 0u : instance_of_read(inst, m, r0);
-#pragma unroll
-    for (uint32_t i = 0; i < kScanPerThread; ++i) {
-        const uint64_t r = r0 + i;
-        if (r >= n) break;
-        while (t + 1 < m && inst[t + 1].read_begin <= r) ++t;
-        const ReadCount rc = count_read(off, off0, r, n, len, check_ends != 0, inst[t].k);
-        const uint64_t s = ws[r] + add;
-        ws[r] = s;
-        if (r + 1 == n) ws[n] = s + rc.windows;
+        const uint64_t r = r0 + 64 * i;
+        const uint64_t inc = narrow ? wave_scan((uint32_t)w[i]) : wave_inclusive_scan(w[i]);
+        const uint64_t a = pre + inc - w[i], z = pre + inc;
+        pre += narrow ? (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)inc, 63) : __shfl(inc, 63, 64);
+        if (r >= n) continue;
+        ws[r] = a;
+        if (r + 1 == n) ws[n] = z;
         // tiles whose first window falls inside this read start here
-        if (tile_read)
-            for (uint64_t tt = (s + tile - 1) / tile; tt * tile < s + rc.windows && tt < tile_cap; ++tt)
+        if (tile_read && w[i])
+            for (uint64_t tt = shift ? (a + tile - 1) >> shift : (a + tile - 1) / tile; tt * tile < z && tt < tile_cap; ++tt)
                 tile_read[tt] = r;
     }
+    if (!last_block) return;
+    // the totals
+    const uint64_t W = before + min(total, kMostOfBlock);
+    uint64_t K = 0;
+    if (single) K = kbefore + min(block_sum(tk, s_wave), kMostOfBlock);
+    if (W > args->max_windows)
+        for (uint32_t i = threadIdx.x; i < m; i += kScanBlock) atomic_or_u32(&st[i].err, kErrInval);
+    if (threadIdx.x != 0) return;
+    cs->windows = W > args->max_windows ? 0 : W;
+    if (!single) return;
+    st[0].windows = W;
+    st[0].inserts = K;
+    if (!plan) return;
+    __threadfence();
+    const Instance &in = inst[0];
+    const uint32_t e = __hip_atomic_load(&st[0].err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!(e & kErrRange) && in.prior_inserts + K > 0xffffffffull) atomic_or_u32(&st[0].err, kErrRange);
+    SortPlan pl{};
+    pl.w_end = W;
+    pl.valid = !(e & (kErrInval | kErrSkip)) && W <= args->max_windows && in.parts;
+    pl.tiles = pl.valid ? (W + tile - 1) / tile : 0;
+    pl.groups = in.fan > 1 ? (pl.tiles + kSortGroup - 1) / kSortGroup : 0;
+    *plan = pl;
+    *tot = SortTotals{pl.tiles, in.fan > 1 ? in.d1 : 0u, pl.groups};
 }
 
 // ---------------------------------------------------------------- build
@@ -909,11 +970,11 @@ uint32_t grid_for(K kernel, int device, uint32_t block) {
 
 // ---------------------------------------------------------------- launchers
 
-hipError_t launch_prepare(const PassArgs *args, Instance *inst, InstStatus *st, CallState *cs,
-                          uint32_t m_cap, hipStream_t s) {
-    const uint32_t threads = 256;
-    const uint32_t blocks = (m_cap + threads - 1) / threads;
-    hipLaunchKernelGGL(k_prepare, dim3(blocks ? blocks : 1), dim3(threads), 0, s, args, inst, st, cs);
+hipError_t launch_begin(const void *host, PassArgs *args, Instance *inst, InstStatus *st, CallState *cs,
+                        uint64_t *done, uint32_t m_cap, hipStream_t s) {
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>(((uint64_t)m_cap * kInstWords + 255) / 256, 64);
+    hipLaunchKernelGGL(k_begin, dim3(blocks), dim3(256), 0, s, static_cast<const uint64_t *>(host), args, inst, st, cs,
+                       done, done ? kDoneWords : 0u);
     return hipGetLastError();
 }
 
@@ -941,20 +1002,16 @@ hipError_t launch_pack(const PassArgs *args, uint64_t *packed, const Instance *i
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const PassArgs *args, const Instance *inst, InstStatus *st, uint64_t *ws,
-                       uint64_t *partials, uint64_t *tile_read, CallState *cs, uint64_t n_cap,
+hipError_t launch_scan(const PassArgs *args, const Instance *inst, InstStatus *st, uint64_t *ws, uint64_t *sums,
+                       uint64_t *tile_read, CallState *cs, SortPlan *plan, SortTotals *tot, uint64_t n_cap,
                        hipStream_t s) {
-    const uint64_t nb = std::max<uint64_t>(1, scan_blocks(n_cap));
-    uint64_t *kpart = partials + nb;  // the partials buffer holds 2 * nb + 1 words
-    hipLaunchKernelGGL(k_scan_local, dim3((uint32_t)nb), dim3(kScanBlock), 0, s, args, inst, st, ws,
-                       partials, kpart);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, args, partials, kpart, nb, cs, st);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scan_add, dim3((uint32_t)nb), dim3(kScanBlock), 0, s, args, inst, ws, partials,
-                       tile_read);
+    const dim3 g((uint32_t)std::max<uint64_t>(1, scan_blocks(n_cap))), b(kScanBlock);
+    if (g.x == 1) {
+        hipLaunchKernelGGL((k_scan<true, true>), g, b, 0, s, args, inst, st, ws, sums, tile_read, cs, plan, tot);
+    } else {
+        hipLaunchKernelGGL((k_scan<true, false>), g, b, 0, s, args, inst, st, ws, sums, tile_read, cs, plan, tot);
+        hipLaunchKernelGGL((k_scan<false, true>), g, b, 0, s, args, inst, st, ws, sums, tile_read, cs, plan, tot);
+    }
     return hipGetLastError();
 }
 

@@ -291,7 +291,7 @@ struct PassSizes {
         tile_cap = dbgk::max_tiles(k.len_cap, T);
         packed = dbgk::packed_words(k.len_cap) * 8;
         ws = (k.n_cap + 1) * 8;
-        partials = std::max<uint64_t>(1, dbgk::scan_blocks(k.n_cap)) * 16 + 8;
+        partials = std::max<uint64_t>(1, (k.n_cap + 1023) / 1024) * 16 + 8;  // scan_words and more
         args = dbgk::kArgsBytes + sizeof(Instance) * k.m_cap;
         status = sizeof(InstStatus) * k.m_cap + sizeof(CallState);
         tiles = k.binned ? 0 : tile_cap * 8;
@@ -318,7 +318,13 @@ inline PassOpts opts_of(const dbg_graph *g);
 inline void fill_args(dbgk::PassArgs &a, const PassKey &k, const PassSizes &z, uint32_t mm, const Instance *hi,
                       const uint8_t *d_reads, uint64_t len, const uint64_t *d_off, uint64_t n, bool check_ends,
                       uint64_t *xkeys, uint32_t *xcounts, uint64_t xcap, const PassOpts &o) {
-    const uint64_t T = (uint64_t)k.shape.block * k.shape.wpt;
+    uint64_t T = (uint64_t)k.shape.block * k.shape.wpt, tile_cap = z.tile_cap;
+    if (k.sorted) {
+        dbgk::SortBuffers sb{};
+        sort_caps(k, sb);
+        T = sb.tile1;
+        tile_cap = sb.tiles1_cap;
+    }
     uint64_t P = 0;
     for (uint32_t i = 0; i < mm; ++i) P += hi[i].parts;
     std::memset(&a, 0, sizeof a);
@@ -327,7 +333,7 @@ inline void fill_args(dbgk::PassArgs &a, const PassKey &k, const PassSizes &z, u
     a.n_reads = n;
     a.reads_len = len;
     a.max_windows = k.binned ? len : (z.tile_cap - 1) * T;
-    a.tile_cap = z.tile_cap;
+    a.tile_cap = tile_cap;
     a.parts_total = P;
     a.m = mm;
     a.check_ends = check_ends ? 1 : 0;
@@ -368,7 +374,8 @@ struct Pass {
     struct Cached {
         PassKey key;
         uint64_t generation;
-        hipGraphExec_t setup, build;
+        bool timed;
+        hipGraphExec_t setup, build;  // build: null when setup holds the whole pass
     };
     std::vector<Cached> graphs;
     uint64_t captures = 0, replays = 0;
@@ -520,19 +527,19 @@ struct Pass {
     }
 
     // The two halves of the pass, enqueued on `s` (directly or under capture).
-    hipError_t enqueue_setup(const PassKey &k, hipStream_t s) {
+    hipError_t enqueue_setup(const PassKey &k, const dbgk::SortBuffers &sb, hipStream_t s) {
         dbgk::PassArgs *da = dargs.as<dbgk::PassArgs>();
         Instance *di = reinterpret_cast<Instance *>(dargs.as<unsigned char>() + dbgk::kArgsBytes);
         InstStatus *dst = dstatus.as<InstStatus>();
         CallState *cs = reinterpret_cast<CallState *>(dst + k.m_cap);
-        hipError_t e = hipMemcpyAsync(dargs.p, hargs.p, dbgk::kArgsBytes + sizeof(Instance) * k.m_cap,
-                                      hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = dbgk::launch_prepare(da, di, dst, cs, k.m_cap, s);
+        const bool planned = k.sorted && k.single;  // the scan makes the plan
+        hipError_t e = dbgk::launch_begin(hargs.p, da, di, dst, cs, sb.done, k.m_cap, s);
         // sorted tiles pack the reads themselves
         if (e == hipSuccess && !k.sorted) e = dbgk::launch_pack(da, packed.as<uint64_t>(), di, dst, k.len_cap, s);
         if (e == hipSuccess)
             e = dbgk::launch_scan(da, di, dst, ws.as<uint64_t>(), partials.as<uint64_t>(),
-                                  k.binned ? nullptr : tiles.as<uint64_t>(), cs, k.n_cap, s);
+                                  planned ? sb.tile_read : k.binned ? nullptr : tiles.as<uint64_t>(), cs,
+                                  planned ? sb.plan : nullptr, sb.totals, k.n_cap, s);
         return e;
     }
     hipError_t enqueue_build(const PassKey &k, const dbgk::BinBuffers &bb, const dbgk::SortBuffers &sb, int device,
@@ -546,8 +553,8 @@ struct Pass {
             e = dbgk::launch_build_wide(da, di, packed.as<uint64_t>(), ws.as<uint64_t>(), tiles.as<uint64_t>(), dst,
                                         cs, k.shape, k.stats != 0, s);
         else if (k.sorted)
-            e = dbgk::launch_sorted(da, di, ws.as<uint64_t>(), dst, sb, k.n_cap, k.stats != 0, s,
-                                    mark ? marks : nullptr);
+            return dbgk::launch_sorted(da, di, ws.as<uint64_t>(), dst, sb, k.n_cap, k.single != 0, k.stats != 0, s,
+                                       mark ? marks : nullptr);  // its reduce stores the statuses
         else if (k.binned)
             e = dbgk::launch_binned(da, di, packed.as<uint64_t>(), ws.as<uint64_t>(), dst, bb, k.n_cap, device,
                                     k.stats != 0, s,
@@ -561,20 +568,23 @@ struct Pass {
         return e;
     }
 
+    // One graph, or two when the halves are timed apart.
     hipError_t capture(const PassKey &k, const dbgk::BinBuffers &bb, const dbgk::SortBuffers &sb, int device,
-                       Cached &out) {
+                       bool time_it, Cached &out) {
         out.key = k;
         out.generation = generation;
+        out.timed = time_it;
         out.setup = out.build = nullptr;
-        for (int half = 0; half < 2; ++half) {
+        for (int part = 0; part < (time_it ? 2 : 1); ++part) {
             hipGraph_t g = nullptr;
             hipError_t e = hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return e;
-            const hipError_t ee =
-                half == 0 ? enqueue_setup(k, cap_stream) : enqueue_build(k, bb, sb, device, cap_stream);
+            hipError_t ee = hipSuccess;
+            if (part == 0) ee = enqueue_setup(k, sb, cap_stream);
+            if (ee == hipSuccess && (part == 1 || !time_it)) ee = enqueue_build(k, bb, sb, device, cap_stream);
             e = hipStreamEndCapture(cap_stream, &g);
             if (ee != hipSuccess) e = ee;
-            if (e == hipSuccess) e = hipGraphInstantiate(half == 0 ? &out.setup : &out.build, g, nullptr, nullptr, 0);
+            if (e == hipSuccess) e = hipGraphInstantiate(part == 0 ? &out.setup : &out.build, g, nullptr, nullptr, 0);
             if (g) (void)hipGraphDestroy(g);
             if (e != hipSuccess) return e;
         }
@@ -600,12 +610,13 @@ struct Pass {
         const PassSizes z(k, bb);
         hipError_t e;
         if ((!k.sorted && (e = grow(packed, z.packed)) != hipSuccess) || (e = grow(ws, z.ws)) != hipSuccess ||
-            (e = grow(partials, z.partials)) != hipSuccess || (e = grow(dargs, z.args)) != hipSuccess ||
+            (e = grow(partials, z.partials + 8 * dbgk::kDoneWords)) != hipSuccess || (e = grow(dargs, z.args)) != hipSuccess ||
             (e = grow(dstatus, z.status)) != hipSuccess || (!binned && (e = grow(tiles, z.tiles)) != hipSuccess) ||
             (k.sorted && (e = reserve_sorted(k, sb)) != hipSuccess) ||
             (binned && !k.sorted && (e = reserve_binned(k, bb)) != hipSuccess))
             return e;
         if (k.sorted) {
+            sb.done = partials.as<uint64_t>() + dbgk::scan_words(k.n_cap);
             sorted_grids(k, device, sb);
             shapes = dbgk::auto_shapes(k.rw, k.d1_cap);
         } else if (binned) {
@@ -613,15 +624,16 @@ struct Pass {
             shapes = (bb.shape1 + 1) | (bb.shape2 + 1) << 8;
         }
         fill_args(*host_args(), k, z, mm, hi, d_reads, len, d_off, n, check_ends, xkeys, xcounts, xcap, o);
+        host_args()->host_status = hstatus.as<InstStatus>();
 
         Cached *c = nullptr;
         if (use_graphs) {
             for (auto &x : graphs)
-                if (x.key == k && x.generation == generation) c = &x;
+                if (x.key == k && x.generation == generation && x.timed == time_it) c = &x;
             if (!c) {
                 if (graphs.size() >= 8 || (!graphs.empty() && graphs[0].generation != generation)) drop_graphs();
                 Cached fresh{};
-                e = capture(k, bb, sb, device, fresh);
+                e = capture(k, bb, sb, device, time_it, fresh);
                 if (e != hipSuccess) {
                     if (fresh.setup) (void)hipGraphExecDestroy(fresh.setup);
                     if (fresh.build) (void)hipGraphExecDestroy(fresh.build);
@@ -634,10 +646,11 @@ struct Pass {
             }
         }
         if (time_it) (void)hipEventRecord(ev_a, s);
-        e = c ? hipGraphLaunch(c->setup, s) : enqueue_setup(k, s);
+        e = c ? hipGraphLaunch(c->setup, s) : enqueue_setup(k, sb, s);
         if (time_it && e == hipSuccess) (void)hipEventRecord(ev_b, s);
         marked = !c && time_it && binned;
-        if (e == hipSuccess) e = c ? hipGraphLaunch(c->build, s) : enqueue_build(k, bb, sb, device, s, marked);
+        if (e == hipSuccess && !c) e = enqueue_build(k, bb, sb, device, s, marked);
+        if (e == hipSuccess && c && c->build) e = hipGraphLaunch(c->build, s);
         if (time_it && e == hipSuccess) (void)hipEventRecord(ev_c, s);
         if (e != hipSuccess) return e;
         m = mm;

@@ -719,6 +719,36 @@ constexpr uint32_t kUnitRecords = kUnitRounds * kReduceBlock;  // a larger unit 
 constexpr uint32_t kUnitTarget = 1800;    // records a unit is meant to have at most
 constexpr uint32_t kStageUnits = 4;       // planned together
 
+// The pass's end: the last workgroup to come here stores the statuses in the
+// host's memory (a copy command after the kernel takes longer).  Whole block.
+// The statuses are written and read by device-wide atomics alone, so all that a
+// workgroup needs before it counts itself is that its own are done: a fence
+// would write back its XCD's whole L2, the table just stored included (100 us
+// more over the 2258 segments of a 4.64 Mbp genome; one counter instead of
+// kDoneLines, 20).
+__device__ __forceinline__ void finish_pass(const PassArgs *args, const InstStatus *st, uint64_t *done, uint32_t *s_last) {
+    if (!done) return;  // uniform
+    __builtin_amdgcn_s_waitcnt(0xf70);  // vmcnt(0)
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t line = blockIdx.x % kDoneLines, lines = min(gridDim.x, kDoneLines);
+        const uint32_t on_line = (gridDim.x - line + kDoneLines - 1) / kDoneLines;
+        const auto last = [&](uint32_t which, uint32_t of) {
+            return __hip_atomic_fetch_add(done + which * kDoneStride, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+                       1 == of;
+        };
+        *s_last = last(line, on_line) && last(kDoneLines, lines);
+    }
+    __syncthreads();
+    if (!*s_last) return;
+    const uint64_t *from = reinterpret_cast<const uint64_t *>(st);
+    uint64_t *to = as_global(reinterpret_cast<uint64_t *>(args->host_status));
+    const uint32_t words = args->m * (uint32_t)(sizeof(InstStatus) / 8);
+    for (uint32_t i = threadIdx.x; i < words; i += kReduceBlock)
+        to[i] = __hip_atomic_load(from + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+static_assert(sizeof(InstStatus) % 8 == 0, "copied in words");
+
 // One workgroup per run of segments.  A segment's records are its pieces laid
 // end to end.  They are read in pairs of units, a unit being up to 128
 // consecutive pieces that a wavefront plans (a scan of the lengths, a bitmap of
@@ -732,7 +762,7 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
     const PassArgs *__restrict__ args, const Instance *__restrict__ inst, const SortPlan *__restrict__ plan,
     const SortBucket *__restrict__ buckets, const uint64_t *__restrict__ tile2_base, const uint16_t *__restrict__ off1,
     const uint16_t *__restrict__ off2, const uint64_t *__restrict__ rec1w, const uint64_t *__restrict__ rec2w,
-    uint32_t row1, uint32_t row2, uint32_t tile1, uint32_t tile2, InstStatus *st) {
+    uint32_t row1, uint32_t row2, uint32_t tile1, uint32_t tile2, InstStatus *st, uint64_t *done) {
     using R = typename RecOf<RW>::T;
     static_assert(RW == 1 || EW == 4, "long keys take 32-byte entries");
     constexpr uint32_t Q = kUnitRecords / 64;
@@ -753,7 +783,11 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
     const uint64_t per_block = (parts_total + gridDim.x - 1) / gridDim.x;
     const uint64_t gp0 = min((uint64_t)blockIdx.x * per_block, parts_total);
     const uint32_t n_gp = (uint32_t)(min(gp0 + per_block, parts_total) - gp0);  // the workgroup's segments
-    if (n_gp == 0) return;
+    const auto finish = [&]() { finish_pass(args, st, done, &s_claims[0]); };
+    if (n_gp == 0) {
+        finish();
+        return;
+    }
     // LDS starts zeroed and every write-back leaves it zeroed again
     for (uint32_t s = tid; s < kSegSlots; s += kReduceBlock) {
         s_key[s] = 0;
@@ -1007,6 +1041,7 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
     }
     if (tid == 0 && inst_claims) atomic_add_u64(&st[cur_inst].claimed, inst_claims);
     if (STATS) ps.flush(args->stats);
+    finish();
 }
 
 // ---------------------------------------------------------------- launches
@@ -1057,14 +1092,15 @@ hipError_t sort_windows(const PassArgs *args, const Instance *inst, const uint64
 
 template <uint32_t RW>
 hipError_t launch_sorted_rw(const PassArgs *args, const Instance *inst, const uint64_t *ws, InstStatus *st,
-                            const SortBuffers &sb, uint64_t n_cap, bool stats, hipStream_t s, hipEvent_t *marks) {
+                            const SortBuffers &sb, uint64_t n_cap, bool single, bool stats, hipStream_t s,
+                            hipEvent_t *marks) {
     using Sh = Shapes<RW>;
     hipError_t e;
     const auto mark = [&](int i) {
         if (marks) (void)hipEventRecord(marks[i], s);
     };
-    hipLaunchKernelGGL(k_sort_plan, dim3(1), dim3(1024), 0, s, args, inst, ws, st, sb.plan, sb.totals, sb.tile1);
-    {
+    if (!single) {  // (the window scan planned a one-instance pass)
+        hipLaunchKernelGGL(k_sort_plan, dim3(1), dim3(1024), 0, s, args, inst, ws, st, sb.plan, sb.totals, sb.tile1);
         const uint32_t g = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((n_cap + 255) / 256, 8192));
         hipLaunchKernelGGL(k_sort_tile_reads, dim3(g), dim3(256), 0, s, args, inst, ws, sb.plan, st, sb.tile_read,
                            sb.tile1);
@@ -1104,7 +1140,7 @@ hipError_t launch_sorted_rw(const PassArgs *args, const Instance *inst, const ui
 #define DBG_LAUNCH_REDUCE(EW, STATS)                                                                              \
     hipLaunchKernelGGL((k_reduce_pieces<EW, RW, STATS>), dim3(sb.grid_reduce), dim3(kReduceBlock), 0, s, args, inst, \
                        sb.plan, sb.buckets, sb.tile2_base, sb.off1, sb.off2, sb.rec1, sb.rec2, sb.row1, sb.row2,  \
-                       sb.tile1, sb.tile2, st)
+                       sb.tile1, sb.tile2, st, sb.done)
     if constexpr (RW == 2) {
         if (stats) DBG_LAUNCH_REDUCE(4, true); else DBG_LAUNCH_REDUCE(4, false);
     } else if (sb.entry_words == 4) {
@@ -1128,9 +1164,10 @@ uint32_t resident(K kernel, int device, uint64_t cap) {
 }  // namespace
 
 hipError_t launch_sorted(const PassArgs *args, const Instance *inst, const uint64_t *ws, InstStatus *st,
-                         const SortBuffers &sb, uint64_t n_cap, bool stats, hipStream_t s, hipEvent_t *marks) {
-    if (sb.rec_words == 2) return launch_sorted_rw<2>(args, inst, ws, st, sb, n_cap, stats, s, marks);
-    return launch_sorted_rw<1>(args, inst, ws, st, sb, n_cap, stats, s, marks);
+                         const SortBuffers &sb, uint64_t n_cap, bool single, bool stats, hipStream_t s,
+                         hipEvent_t *marks) {
+    if (sb.rec_words == 2) return launch_sorted_rw<2>(args, inst, ws, st, sb, n_cap, single, stats, s, marks);
+    return launch_sorted_rw<1>(args, inst, ws, st, sb, n_cap, single, stats, s, marks);
 }
 
 // Dynamic LDS limits of the kernels (process-wide, so always the most any

@@ -194,14 +194,15 @@ extern "C" int dbg_build_device_static(dbg_graph *g, const uint8_t *d_reads, uin
 
     hipLaunchKernelGGL(k_put_args, dim3(1), dim3(64), 0, s, a, hi[0], dargs);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = dbgk::launch_prepare(da, di, dst, cs, key.m_cap, s);
+    if (e == hipSuccess) e = dbgk::launch_begin(nullptr, da, di, dst, cs, nullptr, key.m_cap, s);
     if (e == hipSuccess && !key.sorted) e = dbgk::launch_pack(da, packed, di, dst, key.len_cap, s);
     if (e == hipSuccess)
         e = dbgk::launch_scan(da, di, dst, ws, reinterpret_cast<uint64_t *>(base + o_partials),
-                              binned ? nullptr : reinterpret_cast<uint64_t *>(base + o_tiles), cs, key.n_cap, s);
+                              key.sorted ? sb.tile_read : binned ? nullptr : reinterpret_cast<uint64_t *>(base + o_tiles),
+                              cs, key.sorted ? sb.plan : nullptr, sb.totals, key.n_cap, s);
     if (e == hipSuccess) {
         if (key.sorted)
-            e = dbgk::launch_sorted(da, di, ws, dst, sb, key.n_cap, false, s, nullptr);
+            e = dbgk::launch_sorted(da, di, ws, dst, sb, key.n_cap, true, false, s, nullptr);
         else if (binned)
             e = dbgk::launch_binned(da, di, packed, ws, dst, bb, key.n_cap, g->device, false, s, nullptr);
         else
