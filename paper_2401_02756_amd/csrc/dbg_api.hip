@@ -173,26 +173,30 @@ static int extract_impl(dbg_graph *g, uint64_t *keys, uint32_t *counts, uint64_t
         okeys = g->xkeys.as<uint64_t>();
         ocnt = g->xcnt.as<uint32_t>();
     }
-    if (g->xn.reserve(8) != hipSuccess) return DBG_E_DEVICE;
-    uint64_t found = 0;
-    e = dbgk::launch_fill_zero(g->xn.as<uint64_t>(), 1, s);
-    if (e == hipSuccess && kw == 2 && !g->binned)
-        e = dbgk::launch_extract_wide(g->table.as<uint64_t>(), g->cap, okeys, ocnt, V, g->xn.as<uint64_t>(), s);
-    else if (e == hipSuccess && g->binned)
+    uint64_t found = 0, *total = nullptr;
+    if (g->binned) {
+        if (!(total = g->found.get())) return DBG_E_DEVICE;
+        *total = 0;
         e = dbgk::launch_extract_binned(g->table.as<uint64_t>(), g->ew, (uint32_t)kw, g->parts,
-                                        g->seg_count.as<uint32_t>(), g->seg_off.as<uint64_t>(),
-                                        g->seg_partials.as<uint64_t>(), g->seg_len.as<uint64_t>(), okeys,
-                                        ocnt, V, g->xn.as<uint64_t>(), g->device, s);
-    else if (e == hipSuccess)
-        e = dbgk::launch_extract(g->table.as<uint64_t>(), g->ew, g->cap, okeys, ocnt, V,
-                                 g->xn.as<uint64_t>(), s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&found, g->xn.p, 8, hipMemcpyDeviceToHost, s);
+                                        g->seg_count.as<uint32_t>(), g->seg_sums.as<uint64_t>(), okeys, ocnt, V,
+                                        total, s);
+    } else {
+        if (g->xn.reserve(8) != hipSuccess) return DBG_E_DEVICE;
+        e = dbgk::launch_fill_zero(g->xn.as<uint64_t>(), 1, s);
+        if (e == hipSuccess && kw == 2)
+            e = dbgk::launch_extract_wide(g->table.as<uint64_t>(), g->cap, okeys, ocnt, V, g->xn.as<uint64_t>(), s);
+        else if (e == hipSuccess)
+            e = dbgk::launch_extract(g->table.as<uint64_t>(), g->ew, g->cap, okeys, ocnt, V,
+                                     g->xn.as<uint64_t>(), s);
+        if (e == hipSuccess) e = hipMemcpyAsync(&found, g->xn.p, 8, hipMemcpyDeviceToHost, s);
+    }
     if (e == hipSuccess && !device_out) {
         e = hipMemcpyAsync(keys, okeys, V * 8 * kw, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipMemcpyAsync(counts, ocnt, V * 16, hipMemcpyDeviceToHost, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return DBG_E_DEVICE;
+    if (total) found = *static_cast<volatile uint64_t *>(total);
     return found == V ? DBG_OK : DBG_E_DEVICE;
 }
 
@@ -329,9 +333,9 @@ void dbg_destroy(dbg_graph *g) {
     if (g->pass.pending) (void)g->pass.wait(nullptr, nullptr);
     if (g->stream) (void)hipStreamSynchronize(g->stream);
     DevBuf *bufs[] = {&g->table, &g->reads,     &g->offsets, &g->xkeys,        &g->xcnt,    &g->xn,
-                      &g->nkeys, &g->ncnt,      &g->n8,      &g->seg_count,    &g->seg_off, &g->seg_partials,
-                      &g->seg_len, &g->pstats};
+                      &g->nkeys, &g->ncnt,      &g->n8,      &g->seg_count,    &g->seg_sums, &g->pstats};
     for (DevBuf *b : bufs) b->release();
+    g->found.release();
     g->pass.release();
     dbg_contigs_free(g->contigs);
     if (g->zero_ev) (void)hipEventDestroy(g->zero_ev);

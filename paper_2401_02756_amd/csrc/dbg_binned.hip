@@ -1187,39 +1187,77 @@ __global__ __launch_bounds__(kReduceBlock) void k_reduce(const PassArgs *__restr
 // ---------------------------------------------------------------- extract
 
 constexpr uint32_t kExtractSegBlock = 256;
+constexpr uint32_t kExtractUnroll = 4;  // vertices a thread has in flight
 
-// The vertices of segment gp (packed at its first entries) go to
-// [seg_off[gp], seg_off[gp + 1]).
+// Sums of kExtractGroup segments' vertices each.
+__global__ __launch_bounds__(kExtractSegBlock) void k_extract_sums(const uint32_t *__restrict__ seg_count, uint32_t parts,
+                                                                   uint64_t *__restrict__ sums) {
+    __shared__ uint64_t s_sum;
+    if (threadIdx.x == 0) sums[blockIdx.x] = 0;
+    uint64_t v = 0;
+    for (uint32_t i = threadIdx.x; i < kExtractGroup; i += kExtractSegBlock) {
+        const uint32_t gp = blockIdx.x * kExtractGroup + i;
+        v += gp < parts ? seg_count[gp] : 0;
+    }
+    flush_block_sum(v, sums + blockIdx.x, &s_sum);
+}
+
+// One workgroup per segment: its vertices (packed at its first entries) go
+// behind those of all segments before it, which the workgroup counts itself, by
+// groups where there are more segments than one (sums).  The last stores the
+// total in the host's memory.
+// Bound by latency for a small table, where the five launches before it (clear,
+// set, three scans) and the copy behind it took 60 us more than this does, and
+// by the memory for a large one: 26082 segments in 228 us
+// (258 with 2048 workgroups that take several segments each, 273 where these
+// are neighbours and a thread has one vertex in flight).
 template <uint32_t EW, uint32_t RW>
-__global__ __launch_bounds__(kExtractSegBlock) void k_extract_seg(const uint64_t *__restrict__ table,
-                                                                 uint32_t parts,
-                                                                 const uint64_t *__restrict__ seg_off,
-                                                                 uint64_t *__restrict__ okeys,
-                                                                 uint32_t *__restrict__ ocnt,
-                                                                 uint64_t ocap, uint64_t *out_n) {
-    for (uint32_t gp = blockIdx.x; gp < parts; gp += gridDim.x) {
-        const uint64_t *seg = table + (uint64_t)gp * kSegSlots * EW;
-        const uint64_t base = seg_off[gp];
-        const uint32_t n = (uint32_t)min<uint64_t>(seg_off[gp + 1] - base, kSegSlots);
-        for (uint32_t e = threadIdx.x; e < n; e += blockDim.x) {
+__global__ __launch_bounds__(kExtractSegBlock) void k_extract_seg(const uint64_t *__restrict__ table, uint32_t parts,
+                                                                  const uint32_t *__restrict__ seg_count,
+                                                                  const uint64_t *__restrict__ sums,
+                                                                  uint64_t *__restrict__ okeys,
+                                                                  uint32_t *__restrict__ ocnt, uint64_t ocap,
+                                                                  uint64_t *out_n) {
+    __shared__ uint64_t s_wave[kExtractSegBlock / 64];
+    const uint32_t gp = blockIdx.x, n_all = seg_count[gp];
+    uint64_t base = 0;
+    const uint32_t groups = sums ? gp / kExtractGroup : 0;
+    for (uint32_t i = threadIdx.x; i < groups; i += kExtractSegBlock) base += sums[i];
+    for (uint32_t i = groups * kExtractGroup + threadIdx.x; i < gp; i += kExtractSegBlock) base += seg_count[i];
+    for (int d = 32; d >= 1; d >>= 1) base += __shfl_xor(base, d, 64);
+    if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = base;
+    __syncthreads();
+    base = 0;
+    for (uint32_t w = 0; w < kExtractSegBlock / 64; ++w) base += s_wave[w];
+    const uint64_t *seg = table + (uint64_t)gp * kSegSlots * EW;
+    const uint32_t n = (uint32_t)min<uint64_t>(min(n_all, kSegSlots), ocap > base ? ocap - base : 0);
+    for (uint32_t e0 = threadIdx.x; e0 < n; e0 += kExtractUnroll * kExtractSegBlock) {
+        uint64_t key[kExtractUnroll], low[kExtractUnroll];
+        uint4 cnt[kExtractUnroll];
+#pragma unroll
+        for (uint32_t i = 0; i < kExtractUnroll; ++i) {
+            const uint32_t e = min(e0 + i * kExtractSegBlock, n - 1);
+            key[i] = seg[e];
+            if constexpr (RW == 2) low[i] = seg[kSegSlots + e];
+            cnt[i] = seg_counts<RW>(seg)[e];
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kExtractUnroll; ++i) {
+            const uint32_t e = e0 + i * kExtractSegBlock;
+            if (e >= n) break;
             const uint64_t idx = base + e;
-            if (idx >= ocap) break;
             if constexpr (RW == 1) {
-                okeys[idx] = key_of_image(seg[e] & ~kOccupied);
+                okeys[idx] = key_of_image(key[i] & ~kOccupied);
             } else {  // two key words per record: K >> 64, K mod 2^64
                 uint64_t kh, kl;
-                wide_key(seg[e] & ~kOccupied, seg[kSegSlots + e], kh, kl);
+                wide_key(key[i] & ~kOccupied, low[i], kh, kl);
                 okeys[2 * idx] = kh;
                 okeys[2 * idx + 1] = kl;
             }
-            *reinterpret_cast<uint4 *>(ocnt + 4 * idx) = seg_counts<RW>(seg)[e];
+            *reinterpret_cast<uint4 *>(ocnt + 4 * idx) = cnt[i];
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *out_n = seg_off[parts];
-}
-
-__global__ void k_set_len(uint64_t *len, uint64_t v) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *len = v;
+    if (gp + 1 == parts && threadIdx.x == 0) *out_n = base + n_all;
 }
 
 template <typename K>
@@ -1498,29 +1536,26 @@ void binned_grids(int device, BinBuffers &bb) {
 }
 
 hipError_t launch_extract_binned(const uint64_t *table, uint32_t entry_words, uint32_t key_words, uint32_t parts,
-                                 const uint32_t *seg_count, uint64_t *seg_off, uint64_t *partials,
-                                 uint64_t *len, uint64_t *out_keys, uint32_t *out_counts,
-                                 uint64_t out_cap, uint64_t *out_n, int device, hipStream_t s) {
-    const uint64_t nb = std::max<uint64_t>((parts + kFlatChunk - 1) / kFlatChunk, 1);
-    hipLaunchKernelGGL(k_set_len, dim3(1), dim3(64), 0, s, len, (uint64_t)parts);
-    hipLaunchKernelGGL(k_flat_local, dim3((uint32_t)nb), dim3(kFlatBlock), 0, s, seg_count, len, seg_off,
-                       partials);
-    hipLaunchKernelGGL(k_flat_partials, dim3(1), dim3(1024), 0, s, partials, nb, len, seg_off);
-    hipLaunchKernelGGL(k_flat_add, dim3((uint32_t)nb), dim3(kFlatBlock), 0, s, len, seg_off, partials);
-    if (key_words == 2) {
-        if (entry_words != 4) return hipErrorInvalidValue;
-        const uint32_t g = occupancy_grid(k_extract_seg<4, 2>, device, kExtractSegBlock, parts, 0);
-        hipLaunchKernelGGL((k_extract_seg<4, 2>), dim3(g), dim3(kExtractSegBlock), 0, s, table, parts, seg_off,
-                           out_keys, out_counts, out_cap, out_n);
-    } else if (entry_words == 4) {
-        const uint32_t g = occupancy_grid(k_extract_seg<4, 1>, device, kExtractSegBlock, parts, 0);
-        hipLaunchKernelGGL((k_extract_seg<4, 1>), dim3(g), dim3(kExtractSegBlock), 0, s, table, parts, seg_off,
-                           out_keys, out_counts, out_cap, out_n);
-    } else {
-        const uint32_t g = occupancy_grid(k_extract_seg<3, 1>, device, kExtractSegBlock, parts, 0);
-        hipLaunchKernelGGL((k_extract_seg<3, 1>), dim3(g), dim3(kExtractSegBlock), 0, s, table, parts, seg_off,
-                           out_keys, out_counts, out_cap, out_n);
-    }
+                                 const uint32_t *seg_count, uint64_t *sums, uint64_t *out_keys,
+                                 uint32_t *out_counts, uint64_t out_cap, uint64_t *out_n, hipStream_t s) {
+    if (key_words == 2 && entry_words != 4) return hipErrorInvalidValue;
+    // The counts before a segment are up to four loads a thread in one group; beyond,
+    // a launch of 5 us and a gap of 4 keeps it at that.
+    if (parts <= kExtractGroup)
+        sums = nullptr;
+    else
+        hipLaunchKernelGGL(k_extract_sums, dim3((parts + kExtractGroup - 1) / kExtractGroup), dim3(kExtractSegBlock), 0, s,
+                           seg_count, parts, sums);
+    const dim3 g(parts), b(kExtractSegBlock);
+    if (key_words == 2)
+        hipLaunchKernelGGL((k_extract_seg<4, 2>), g, b, 0, s, table, parts, seg_count, sums, out_keys, out_counts,
+                           out_cap, out_n);
+    else if (entry_words == 4)
+        hipLaunchKernelGGL((k_extract_seg<4, 1>), g, b, 0, s, table, parts, seg_count, sums, out_keys, out_counts,
+                           out_cap, out_n);
+    else
+        hipLaunchKernelGGL((k_extract_seg<3, 1>), g, b, 0, s, table, parts, seg_count, sums, out_keys, out_counts,
+                           out_cap, out_n);
     return hipGetLastError();
 }
 

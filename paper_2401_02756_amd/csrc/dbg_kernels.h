@@ -377,16 +377,16 @@ hipError_t launch_binned(const PassArgs *args, const Instance *inst, const uint6
                          const uint64_t *ws, InstStatus *st, const BinBuffers &bb, uint64_t n_cap,
                          int device, bool stats, hipStream_t s, hipEvent_t *marks);
 
-// Extraction of a binned table: seg_count (parts entries) is scanned into
-// seg_off (parts + 1 entries, using `partials` of ceil(parts / 1024) + 1
-// entries and a device word `len` that the call fills with parts), then each
-// segment writes its vertices at its offset (segment order; unspecified
-// order within a segment).  *out_n receives the total on the device.
+// Extraction of a binned table: each segment's vertices behind those of the
+// segments before it (seg_count; unspecified order within a segment).  sums:
+// extract_groups words of scratch.  *out_n, in memory that the host reads
+// after the stream, receives the total.
 // key_words = 2: long keys, written as two words per record.
+constexpr uint32_t kExtractGroup = 1024;
+inline uint64_t extract_groups(uint64_t parts) { return (parts + kExtractGroup - 1) / kExtractGroup; }
 hipError_t launch_extract_binned(const uint64_t *table, uint32_t entry_words, uint32_t key_words, uint32_t parts,
-                                 const uint32_t *seg_count, uint64_t *seg_off, uint64_t *partials,
-                                 uint64_t *len, uint64_t *out_keys, uint32_t *out_counts,
-                                 uint64_t out_cap, uint64_t *out_n, int device, hipStream_t s);
+                                 const uint32_t *seg_count, uint64_t *sums, uint64_t *out_keys,
+                                 uint32_t *out_counts, uint64_t out_cap, uint64_t *out_n, hipStream_t s);
 
 // Occupancy-derived persistent grid for the build kernel (k <= 32) and for
 // the long-k build.

@@ -73,6 +73,61 @@ struct HostBuf {
     T *as() const { return static_cast<T *>(p); }
 };
 
+// One word of pinned memory, which a kernel can store to.  Words come from
+// pages shared by the process: pinning memory takes longer than an extraction.
+// A page is freed with its last word, unless it is the only one.
+class PinnedWord {
+  public:
+    uint64_t *get() {  // null: no memory
+        if (p_) return p_;
+        std::lock_guard<std::mutex> lock(mutex());
+        for (Page &x : pages())
+            if (!x.free.empty()) return take(x);
+        Page x;
+        if (hipHostMalloc(&x.p, kPage, hipHostMallocPortable) != hipSuccess) return nullptr;
+        for (uint32_t i = 0; i < kPage / 8; ++i) x.free.push_back(static_cast<uint64_t *>(x.p) + i);
+        pages().push_back(std::move(x));
+        return take(pages().back());
+    }
+    void release() {
+        if (!p_) return;
+        std::lock_guard<std::mutex> lock(mutex());
+        for (auto x = pages().begin(); x != pages().end(); ++x)
+            if (x->p == page_) {
+                x->free.push_back(p_);
+                if (x->free.size() == kPage / 8 && pages().size() > 1) {
+                    (void)hipHostFree(x->p);
+                    pages().erase(x);
+                }
+                break;
+            }
+        p_ = nullptr;
+    }
+
+  private:
+    static constexpr size_t kPage = 4096;
+    struct Page {
+        void *p = nullptr;
+        std::vector<uint64_t *> free;
+    };
+    static std::mutex &mutex() {
+        static std::mutex m;
+        return m;
+    }
+    static std::vector<Page> &pages() {
+        static auto *v = new std::vector<Page>;  // outlives the handles a program never closes
+        return *v;
+    }
+    uint64_t *take(Page &x) {
+        p_ = x.free.back();
+        page_ = x.p;
+        x.free.pop_back();
+        return p_;
+    }
+    uint64_t *p_ = nullptr;
+    void *page_ = nullptr;
+};
+
 // Makes `device` current for the scope of a call and restores the caller's.
 struct DeviceGuard {
     int prev = -1;
@@ -716,7 +771,7 @@ struct dbg_graph {
     bool binned = false;     // table cut into segments, built by the binned kernels
     bool fresh = true;       // binned: logically empty (contents need not be zero)
     uint32_t parts = 0, d1 = 0, fan = 0;
-    dbgrt::DevBuf seg_count, seg_off, seg_partials, seg_len;  // binned: per-segment occupancy
+    dbgrt::DevBuf seg_count, seg_sums;  // binned: per-segment occupancy, scratch of the extraction
 
     // A zero fill enqueued on `stream` (direct tables) that a build enqueued
     // on another stream must wait for.
@@ -731,6 +786,7 @@ struct dbg_graph {
     uint32_t pending_k = 0;
     dbgrt::DevBuf reads, offsets;   // staging of host input
     dbgrt::DevBuf xkeys, xcnt, xn;  // extraction staging
+    dbgrt::PinnedWord found;        // vertices an extraction found (binned)
     dbgrt::DevBuf pstats;           // probe statistics (DBG_F_STATS): dbgk::kStatWords words
     dbgrt::DevBuf nkeys, ncnt, n8;  // normalized extraction staging
 
@@ -810,9 +866,7 @@ inline hipError_t allocate_table(dbg_graph *g, uint64_t cap) {
         cap = parts * dbgk::kSegSlots;
         hipError_t e;
         if ((e = g->seg_count.reserve(4 * parts)) != hipSuccess ||
-            (e = g->seg_off.reserve(8 * (parts + 1))) != hipSuccess ||
-            (e = g->seg_partials.reserve(8 * ((parts + 1023) / 1024 + 2))) != hipSuccess ||
-            (e = g->seg_len.reserve(8)) != hipSuccess)
+            (e = g->seg_sums.reserve(8 * dbgk::extract_groups(parts))) != hipSuccess)
             return e;
     }
     g->cap = cap;
