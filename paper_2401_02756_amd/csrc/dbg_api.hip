@@ -138,10 +138,9 @@ int dbg_build(dbg_graph *g, const char *reads, const uint64_t *offsets, uint64_t
         (e = g->offsets.reserve((n_reads + 1) * 8)) != hipSuccess)
         return hip_code(e);
     hipStream_t s = g->stream;
-    if (len && hipMemcpyAsync(g->reads.p, reads + base, len, hipMemcpyHostToDevice, s) != hipSuccess)
-        return DBG_E_DEVICE;
-    if (hipMemcpyAsync(g->offsets.p, offsets, (n_reads + 1) * 8, hipMemcpyHostToDevice, s) != hipSuccess)
-        return DBG_E_DEVICE;
+    const HostStage::Span in[] = {{len ? const_cast<char *>(reads + base) : nullptr, g->reads.p, len},
+                                  {const_cast<uint64_t *>(offsets), g->offsets.p, (n_reads + 1) * 8}};
+    if (g->stage.move(in, 2, false, g->device, s) != hipSuccess) return DBG_E_DEVICE;
     rc = enqueue_single(g, g->reads.as<uint8_t>(), len, g->offsets.as<uint64_t>(), n_reads, k, s);
     if (rc != DBG_OK) return rc;
     return harvest(g);
@@ -191,8 +190,8 @@ static int extract_impl(dbg_graph *g, uint64_t *keys, uint32_t *counts, uint64_t
         if (e == hipSuccess) e = hipMemcpyAsync(&found, g->xn.p, 8, hipMemcpyDeviceToHost, s);
     }
     if (e == hipSuccess && !device_out) {
-        e = hipMemcpyAsync(keys, okeys, V * 8 * kw, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(counts, ocnt, V * 16, hipMemcpyDeviceToHost, s);
+        const HostStage::Span out[] = {{keys, okeys, V * 8 * kw}, {counts, ocnt, V * 16}};
+        e = g->stage.move(out, 2, true, g->device, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return DBG_E_DEVICE;
@@ -271,10 +270,9 @@ int dbg_extract_normalized(dbg_graph *g, uint64_t genome_size, uint32_t flags, u
     const bool u8 = (flags & DBG_NORM_U8) != 0;
     e = dbgk::launch_normalize(g->ncnt.as<uint32_t>(), 4 * V, genome_size, g->inserts,
                                u8 ? g->n8.as<uint8_t>() : nullptr, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(keys, g->nkeys.p, V * 8 * kw, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(counts, u8 ? g->n8.p : g->ncnt.p, u8 ? V * 4 : V * 16, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    const HostStage::Span out[] = {{keys, g->nkeys.p, V * 8 * kw},
+                                   {counts, u8 ? g->n8.p : g->ncnt.p, u8 ? V * 4 : V * 16}};
+    if (e == hipSuccess) e = g->stage.move(out, 2, true, g->device, s);
     return e == hipSuccess ? DBG_OK : DBG_E_DEVICE;
 }
 
@@ -336,6 +334,7 @@ void dbg_destroy(dbg_graph *g) {
                       &g->nkeys, &g->ncnt,      &g->n8,      &g->seg_count,    &g->seg_sums, &g->pstats};
     for (DevBuf *b : bufs) b->release();
     g->found.release();
+    g->stage.release();
     g->pass.release();
     dbg_contigs_free(g->contigs);
     if (g->zero_ev) (void)hipEventDestroy(g->zero_ev);
