@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kScanThreads) void k_walk_scan_add(uint64_t *v, uin
 
 // Spell the walks.  The walks of a workgroup lie side by side in seq: where they
 // fit its LDS they are put together there and stored in whole lines.
-// 142 us for the 0.9 million contigs of a 5 Mbp genome at 30x; 1354 when
+// 142 us for the contigs of a 5 Mbp genome at 30x; 1354 when
 // each thread followed its walk again and stored its bytes one by one.
 constexpr uint32_t kWriteBytes = 24 * 1024 - 32;  // six workgroups to a CU
 
