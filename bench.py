@@ -112,23 +112,29 @@ def committed_traffic(profile: str, workload: dict, kernel: str) -> int | None:
     return int(v) if v else None
 
 
-def binned_kernel_bytes(n_reads: int, total_bases: int, windows: int, vertices: int, fused: bool) -> dict:
+def binned_kernel_bytes(n_reads: int, total_bases: int, windows: int, vertices: int, fused: bool,
+                        tiles: bool) -> dict:
     """Algorithmic bytes of each kernel group of a binned build of one-word
     records into an empty table (8-byte window records, 24-byte vertex
     entries); None where the work is bookkeeping of a size the host does not
-    know (plans, histogram scans, segment starts):
-      setup     ASCII in, packed reads out, offsets in, window prefix out;
-      count1    packed reads and each read's offset and window start read;
-      scatter1  the same, and every window's record written;
-      count2    records read;
+    know (plans, histogram scans, segment starts) or where there is none.
+    With automatic scatter shapes the partition sorts tiles (`tiles`):
+      setup     offsets in, window prefix out;
+      scatter1  ASCII and each read's offset and window start in, every
+                window's record out;
       scatter2  records read and written;
       reduce    records read, packed vertex entries written and, with the
-                fused extraction, every vertex's key and counters written."""
+                fused extraction, every vertex's key and counters written.
+    With set shapes the reads are packed in setup, and each scatter has a
+    count before it that reads what it reads."""
+    reduce_bytes = 8 * windows + 24 * vertices * (2 if fused else 1)
+    none = {"plan": None, "count1": None, "scan1": None, "plan2": None, "count2": None, "scan2": None, "starts": None}
+    if tiles:
+        return dict(none, setup=24 * n_reads, scatter1=total_bases + 16 * n_reads + 8 * windows,
+                    scatter2=16 * windows, reduce=reduce_bytes)
     packed = total_bases // 4 + 16 * n_reads
-    return {"setup": total_bases + total_bases // 4 + 24 * n_reads, "plan": None, "count1": packed,
-            "scan1": None, "scatter1": packed + 8 * windows, "plan2": None, "count2": 8 * windows,
-            "scan2": None, "scatter2": 16 * windows, "starts": None,
-            "reduce": 8 * windows + 24 * vertices * (2 if fused else 1)}
+    return dict(none, setup=total_bases + total_bases // 4 + 24 * n_reads, count1=packed,
+                scatter1=packed + 8 * windows, count2=8 * windows, scatter2=16 * windows, reduce=reduce_bytes)
 
 
 def scope_step_bytes(inserts: int, total_bases: int, capacity: int, vertices: int) -> int:
@@ -408,24 +414,28 @@ def measure_step(dbg, torch, dev, rs, inserts: int, mode: str, lf: float, steps:
 
 
 def kernel_roofline(dbg, rs, windows: int, inserts: int, V: int, cap: int, ms_step: float, phases: list,
-                    mode: str, lf: float, entry_bytes: int, workload: str, profile: str) -> tuple:
+                    mode: str, lf: float, entry_bytes: int, workload: str, profile: str, tiles: bool) -> tuple:
     """Per-kernel phase table, and the roofline of the longest kernel group
     (plus the whole step under the scope table's byte model)."""
     table = []
     if mode == "binned":
-        kb = binned_kernel_bytes(rs.n_reads, rs.total_bases, windows, V, True)
+        kb = binned_kernel_bytes(rs.n_reads, rs.total_bases, windows, V, True, tiles)
         for name, ms in zip(dbg.BINNED_PHASES, phases):
             b = kb[name]
             table.append({"phase": name, "ms": round(ms, 4), "algorithmic_bytes": b,
                           "gbs": round(b / (ms * 1e-3) / 1e9, 1) if b and ms > 0 else None})
         cand = [p for p in table if p["algorithmic_bytes"] and p["phase"] != "setup"]
         dom = max(cand, key=lambda p: p["ms"])
-        kernels = {"count1": "k_bin<false> (pass-1 count)", "scatter1": "k_bin<true> (pass-1 scatter)",
-                   "count2": "k_refine<false> (pass-2 count)", "scatter2": "k_refine<true> (pass-2 scatter)",
-                   "reduce": "k_reduce (segment reduce with the fused extraction)"}
-        kname, k_ms, bytes_alg = kernels[dom["phase"]], dom["ms"], dom["algorithmic_bytes"]
-        short = {"count1": "k_bin_count", "scatter1": "k_bin_scatter", "count2": "k_refine_count",
-                 "scatter2": "k_refine_scatter", "reduce": "k_reduce"}[dom["phase"]]
+        if tiles:
+            kernels = {"scatter1": ("k_sort_windows", "windows sorted by bucket, tile by tile"),
+                       "scatter2": ("k_sort_bucket", "each bucket sorted by segment, tile by tile"),
+                       "reduce": ("k_reduce_pieces", "segment reduce with the fused extraction")}
+        else:
+            kernels = {"count1": ("k_bin_count", "pass-1 count"), "scatter1": ("k_bin_scatter", "pass-1 scatter"),
+                       "count2": ("k_refine_count", "pass-2 count"), "scatter2": ("k_refine_scatter", "pass-2 scatter"),
+                       "reduce": ("k_reduce", "segment reduce with the fused extraction")}
+        short, what = kernels[dom["phase"]]
+        kname, k_ms, bytes_alg = "%s (%s)" % (short, what), dom["ms"], dom["algorithmic_bytes"]
     else:
         bytes_alg = algorithmic_bytes(rs.n_reads, rs.total_bases, windows, inserts, V)
         k_ms = phases[-1] if phases else 0.0
@@ -532,7 +542,8 @@ def main() -> int:
                                                   wpt, merge, shape)
         table, roof = kernel_roofline(dbg, rs, rs.windows, rs.inserts, r["V"], r["cap"], r["ms_step"],
                                       pr["phases"], mode, lf, r["st"]["entry_bytes"], names[cfg],
-                                      profile % names[cfg])
+                                      profile % names[cfg], not (shape or {}).get("bin_shape1") and
+                                      not (shape or {}).get("bin_shape2"))
         return dict(r=r, phases=table, roofline=roof)
 
     def long_k_rate(rs, k: int, binned: bool, lf: float, steps: int = 5) -> dict:

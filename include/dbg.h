@@ -119,7 +119,11 @@ typedef struct {
     uint32_t block_size;         /* build kernel threads per block; 0 = 256 */
     uint32_t windows_per_thread; /* windows per thread per tile; 0 = 4 */
     void *stream;                /* hipStream_t for all work; NULL = own stream */
-    /* binned build launch shape: the partition passes work on chunks of
+    /* binned build launch shape.  With bin_shape1 and bin_shape2 both 0
+     * (automatic) the partition sorts tiles of records, without counting
+     * passes, in one level up to 1024 table segments and in two beyond; the
+     * rest of this comment does not apply.  Otherwise the partition passes
+     * count and scatter, and work on chunks of
      * consecutive tiles, about bin_chunks per resident scatter workgroup
      * (0 = 32; at most 16384 chunks a pass).  bin_shape1 and bin_shape2
      * set the shape of the first and second partition scatter: 1 = plain
@@ -129,9 +133,9 @@ typedef struct {
      * lines are stored; 3 = big tiles of 128 KB of records (16384, or
      * 8192 for k > 32; in the first scatter for k <= 31 up to 384 runs,
      * 8192 records in 64 KB), runs two to four times longer; 4 = big
-     * tiles of 128 KB in every case; 0 = automatic (big tiles for the
-     * second scatter, and for the first when k <= 31 or beyond 384 runs,
-     * else plain tiles).  A shape whose LDS does not fit one workgroup
+     * tiles of 128 KB in every case; 0 where the other is set: big tiles for
+     * the second scatter, and for the first when k <= 31 or beyond 384 runs,
+     * else plain tiles.  A shape whose LDS does not fit one workgroup
      * falls back to a smaller one.
      * bin_scatter_div divides the resident grid of a second scatter of
      * plain tiles (0 = automatic: 2 when a level-1 bucket spans more than
@@ -285,12 +289,14 @@ int dbg_reset(dbg_graph *g);
 int dbg_get_stats(dbg_graph *g, dbg_stats *out);
 
 /* Device time of each phase of the handle's last timed build (DBG_F_TIMING),
- * in ms, in this order: setup (argument copy, prepare, pack, window scan),
- * then, for a binned build launched without a graph, ten phases -- plan,
- * pass-1 count, pass-1 scan, pass-1 scatter, pass-2 plan, pass-2 count,
- * pass-2 scan, pass-2 scatter, segment starts, segment reduce -- else the
- * whole build.  Writes min(cap, *n_phases) values; *n_phases is 0 before any
- * timed build. */
+ * in ms, in this order: setup (arguments, pack, window scan), then, for a
+ * binned build launched without a graph, ten phases -- plan, pass-1 count,
+ * pass-1 scan, pass-1 scatter, pass-2 plan, pass-2 count, pass-2 scan, pass-2
+ * scatter, segment starts, segment reduce -- else the whole build.  Phases that
+ * a build does not have read about zero: the counts, their scans, the packing
+ * and the starts where the partition sorts tiles (its levels are the two
+ * scatters), the second of them too where one is enough.  Writes
+ * min(cap, *n_phases) values; *n_phases is 0 before any timed build. */
 int dbg_get_phase_times(dbg_graph *g, double *ms, uint32_t cap, uint32_t *n_phases);
 
 /* Probe statistics of the handle's builds (synchronises first).  All zero for

@@ -730,8 +730,7 @@ constexpr uint32_t kStageUnits = 4;       // planned together
 // The statuses are written and read by device-wide atomics alone, so all that a
 // workgroup needs before it counts itself is that its own are done: a fence
 // would write back its XCD's whole L2, the table just stored included (100 us
-// more over the 2258 segments of a 4.64 Mbp genome; one counter instead of
-// kDoneLines, 20).
+// more for a 5 Mbp genome at 30x; one counter instead of kDoneLines, 20).
 __device__ __forceinline__ void finish_pass(const PassArgs *args, const InstStatus *st, uint64_t *done, uint32_t *s_last) {
     if (!done) return;  // uniform
     __builtin_amdgcn_s_waitcnt(0xf70);  // vmcnt(0)
