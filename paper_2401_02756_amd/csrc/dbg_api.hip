@@ -172,10 +172,10 @@ static int extract_impl(dbg_graph *g, uint64_t *keys, uint32_t *counts, uint64_t
         okeys = g->xkeys.as<uint64_t>();
         ocnt = g->xcnt.as<uint32_t>();
     }
-    uint64_t found = 0, *total = nullptr;
+    uint64_t *total = g->found.get();
+    if (!total) return DBG_E_DEVICE;
+    *total = 0;
     if (g->binned) {
-        if (!(total = g->found.get())) return DBG_E_DEVICE;
-        *total = 0;
         e = dbgk::launch_extract_binned(g->table.as<uint64_t>(), g->ew, (uint32_t)kw, g->parts,
                                         g->seg_count.as<uint32_t>(), g->seg_sums.as<uint64_t>(), okeys, ocnt, V,
                                         total, s);
@@ -187,7 +187,7 @@ static int extract_impl(dbg_graph *g, uint64_t *keys, uint32_t *counts, uint64_t
         else if (e == hipSuccess)
             e = dbgk::launch_extract(g->table.as<uint64_t>(), g->ew, g->cap, okeys, ocnt, V,
                                      g->xn.as<uint64_t>(), s);
-        if (e == hipSuccess) e = hipMemcpyAsync(&found, g->xn.p, 8, hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = dbgk::launch_store_words(g->xn.as<uint64_t>(), total, 1, s);
     }
     if (e == hipSuccess && !device_out) {
         const HostStage::Span out[] = {{keys, okeys, V * 8 * kw}, {counts, ocnt, V * 16}};
@@ -195,8 +195,7 @@ static int extract_impl(dbg_graph *g, uint64_t *keys, uint32_t *counts, uint64_t
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return DBG_E_DEVICE;
-    if (total) found = *static_cast<volatile uint64_t *>(total);
-    return found == V ? DBG_OK : DBG_E_DEVICE;
+    return *static_cast<volatile uint64_t *>(total) == V ? DBG_OK : DBG_E_DEVICE;
 }
 
 int dbg_build_extract_device(dbg_graph *g, const uint8_t *d_reads, uint64_t reads_len,

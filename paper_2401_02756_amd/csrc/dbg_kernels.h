@@ -331,6 +331,8 @@ inline uint64_t max_tiles(uint64_t bytes, uint64_t tile) { return bytes / tile +
 hipError_t launch_begin(const void *host, PassArgs *args, Instance *inst, InstStatus *st, CallState *cs,
                         uint64_t *done, uint32_t m_cap, hipStream_t s);
 hipError_t launch_fill_zero(uint64_t *words, uint64_t n_words, hipStream_t s);
+// n > 0 words from device memory to pinned host memory.
+hipError_t launch_store_words(const uint64_t *from, uint64_t *to, uint64_t n, hipStream_t s);
 // out[i] = src[idx[i]] for i < n (device arrays).
 hipError_t launch_gather_u64(const uint64_t *src, const uint64_t *idx, uint64_t n, uint64_t *out, hipStream_t s);
 hipError_t launch_pack(const PassArgs *args, uint64_t *packed, const Instance *inst, InstStatus *st,

@@ -67,6 +67,13 @@ __global__ void k_begin(const uint64_t *host, PassArgs *args, Instance *inst, In
     if (x == 0) *cs = CallState{};
 }
 
+// Words for the host, in its pinned memory: a kernel behind another costs 5 us,
+// the runtime's copy of a few bytes 10 to 20.
+__global__ void k_store_words(const uint64_t *from, uint64_t *to, uint64_t n) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+        to[i] = from[i];
+}
+
 __global__ void k_fill_zero(uint64_t *__restrict__ words, uint64_t n_words) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     const uint64_t pairs = n_words >> 1;
@@ -991,6 +998,11 @@ hipError_t launch_begin(const void *host, PassArgs *args, Instance *inst, InstSt
     const uint32_t blocks = (uint32_t)std::min<uint64_t>(((uint64_t)m_cap * kInstWords + 255) / 256, 64);
     hipLaunchKernelGGL(k_begin, dim3(blocks), dim3(256), 0, s, static_cast<const uint64_t *>(host), args, inst, st, cs,
                        done, done ? kDoneWords : 0u);
+    return hipGetLastError();
+}
+
+hipError_t launch_store_words(const uint64_t *from, uint64_t *to, uint64_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_store_words, dim3((uint32_t)std::min<uint64_t>((n + 255) / 256, 256)), dim3(256), 0, s, from, to, n);
     return hipGetLastError();
 }
 

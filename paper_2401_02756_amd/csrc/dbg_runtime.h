@@ -732,8 +732,8 @@ struct Pass {
             e = dbgk::launch_build(da, di, packed.as<uint64_t>(), ws.as<uint64_t>(), tiles.as<uint64_t>(), dst,
                                    cs, k.shape, k.single != 0, k.stats != 0, s);
         if (e == hipSuccess)
-            e = hipMemcpyAsync(hstatus.p, dstatus.p, sizeof(InstStatus) * k.m_cap + sizeof(CallState),
-                               hipMemcpyDeviceToHost, s);
+            e = dbgk::launch_store_words(dstatus.as<uint64_t>(), hstatus.as<uint64_t>(),
+                                         (sizeof(InstStatus) * k.m_cap + sizeof(CallState)) / 8, s);
         return e;
     }
 
@@ -901,7 +901,7 @@ struct dbg_graph {
     dbgrt::DevBuf reads, offsets;   // staging of host input
     dbgrt::DevBuf xkeys, xcnt, xn;  // extraction staging
     dbgrt::HostStage stage;         // host input and results
-    dbgrt::PinnedWord found;        // vertices an extraction found (binned)
+    dbgrt::PinnedWord found;        // vertices an extraction found
     dbgrt::DevBuf pstats;           // probe statistics (DBG_F_STATS): dbgk::kStatWords words
     dbgrt::DevBuf nkeys, ncnt, n8;  // normalized extraction staging
 
