@@ -332,9 +332,11 @@ int dbg_build_batch(dbg_graph *const *graphs, const dbg_input *inputs, uint32_t 
  * [read_begin[i], read_begin[i+1]) of d_reads/d_offsets (read j is
  * d_reads[d_offsets[j] - d_offsets[0] .. d_offsets[j+1] - d_offsets[0]),
  * d_offsets has read_begin[m] + 1 entries, d_offsets[read_begin[m]] -
- * d_offsets[0] == reads_len).  read_begin (m + 1 entries, read_begin[0] == 0)
- * and ks (m entries) are host arrays.  A graph that fails a host check keeps
- * its reads in the launch but they are skipped.  Synchronous. */
+ * d_offsets[0] == reads_len).  read_begin (m + 1 entries, read_begin[0] == 0,
+ * none below the one before it; otherwise nothing is launched and every
+ * status is DBG_E_INVAL) and ks (m entries) are host arrays.  A graph that
+ * fails a host check keeps its reads in the launch but they are skipped.
+ * Synchronous. */
 int dbg_build_batch_device(dbg_graph *const *graphs, uint32_t m, const uint64_t *read_begin,
                            const uint32_t *ks, const uint8_t *d_reads, uint64_t reads_len,
                            const uint64_t *d_offsets, int32_t *statuses, void *stream);

@@ -498,7 +498,11 @@ int dbg_build_batch_device(dbg_graph *const *graphs, uint32_t m, const uint64_t 
         return DBG_E_INVAL;
     for (uint32_t i = 0; i < m; ++i)
         if (!graphs[i]) return DBG_E_INVAL;
-    if (read_begin[0] != 0) return DBG_E_INVAL;
+    // the launch attributes each read to one graph by a search of read_begin
+    if (read_begin[0] != 0 || !std::is_sorted(read_begin, read_begin + m + 1)) {
+        std::fill(statuses, statuses + m, DBG_E_INVAL);
+        return DBG_E_INVAL;
+    }
     const int device = graphs[0]->device;
     DeviceGuard guard(device);
     if (!guard.ok) return DBG_E_DEVICE;

@@ -1156,7 +1156,8 @@ struct BatchRun {
 };
 
 // Enqueue one batched pass (not waiting for it): graphs[i] takes reads
-// [read_begin[i], read_begin[i+1]) of the device-resident concatenation.  A
+// [read_begin[i], read_begin[i+1]) of the device-resident concatenation;
+// read_begin does not decrease.  A
 // graph that fails a host-side check stays in the launch as a skipped
 // instance, so its reads are attributed to it and never touched; its status
 // is final here.  The others get their status from batch_finish.
@@ -1177,7 +1178,6 @@ inline void batch_enqueue(dbg_graph *const *graphs, uint32_t m, const uint64_t *
         dbg_graph *g = graphs[i];
         int rc = check_common(g, ks[i]);
         if (rc == DBG_OK && g->device != device) rc = DBG_E_INVAL;
-        if (rc == DBG_OK && read_begin[i + 1] < read_begin[i]) rc = DBG_E_INVAL;
         for (uint32_t j = 0; rc == DBG_OK && j < i; ++j)
             if (graphs[j] == g) rc = DBG_E_INVAL;  // one graph per instance
         if (rc == DBG_OK && g->pass.pending) rc = harvest(g);

@@ -176,6 +176,20 @@ def test_host_side_argument_errors_need_no_device():
     assert all(c.flags == dbg.F_BINNED and 0 < c.load_factor < dbg.BINNED_MAX_LOAD for c in dbg.autotune_space(True))
 
 
+@pytest.mark.parametrize("begin", [(0, 100, 50, 200), (0, 100, 50), (0, 5, 0), (0, 3, 1, 2, 0), (1, 4)])
+def test_batch_read_ranges_must_not_decrease(begin):
+    """Ranges that overlap or end before they begin would have the kernels look
+    reads up in an unsorted table: the whole call is refused on the host."""
+    m = len(begin) - 1
+    dummy = ctypes.create_string_buffer(1 << 16)  # refused before any handle is looked at
+    graphs = (ctypes.c_void_p * m)(*[ctypes.addressof(dummy)] * m)
+    rb, ks = (ctypes.c_uint64 * (m + 1))(*begin), (ctypes.c_uint32 * m)(*[21] * m)
+    st = (ctypes.c_int32 * m)()
+    rc = dbg.lib().dbg_build_batch_device(graphs, m, rb, ks, ctypes.addressof(dummy), 8, ctypes.addressof(dummy), st, None)
+    assert rc == dbg.E_INVAL
+    assert list(st) == [dbg.E_INVAL] * m
+
+
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(dbg, "_lib", None)
     monkeypatch.setattr(dbg, "LIB_PATH", str(tmp_path / "nope.so"))
