@@ -28,6 +28,13 @@ namespace dbgrt {
 
 constexpr uint64_t kCounterLimit = 0xffffffffull;
 
+// The code of a failed call whose caller deals with it: the runtime would
+// otherwise hand the same error to the next check after a launch.
+inline hipError_t settled(hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 // Grow-only device buffer.
 struct DevBuf {
     void *p = nullptr;
@@ -40,7 +47,7 @@ struct DevBuf {
         }
         p = nullptr;
         bytes = 0;
-        hipError_t e = hipMalloc(&p, want);
+        hipError_t e = settled(hipMalloc(&p, want));
         if (e == hipSuccess) bytes = want;
         return e;
     }
@@ -62,7 +69,7 @@ struct HostBuf {
         if (p) (void)hipHostFree(p);
         p = nullptr;
         bytes = 0;
-        hipError_t e = hipHostMalloc(&p, want, hipHostMallocDefault);
+        hipError_t e = settled(hipHostMalloc(&p, want, hipHostMallocDefault));
         if (e == hipSuccess) bytes = want;
         return e;
     }
@@ -86,7 +93,7 @@ class PinnedWord {
         for (Page &x : pages())
             if (!x.free.empty()) return take(x);
         Page x;
-        if (hipHostMalloc(&x.p, kPage, hipHostMallocPortable) != hipSuccess) return nullptr;
+        if (settled(hipHostMalloc(&x.p, kPage, hipHostMallocPortable)) != hipSuccess) return nullptr;
         for (uint32_t i = 0; i < kPage / 8; ++i) x.free.push_back(static_cast<uint64_t *>(x.p) + i);
         pages().push_back(std::move(x));
         return take(pages().back());
@@ -235,7 +242,7 @@ class HostStage {
     bool reserve() {
         if (pinned_.reserve(2 * kWorkers * kChunk) != hipSuccess) return false;
         for (auto &ev : event_)
-            if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) return false;
+            if (!ev && settled(hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return false;
         return true;
     }
     HostBuf pinned_;
