@@ -145,7 +145,10 @@ class PinnedWord {
 // reads and its 124 MB of vertices took 13.3 ms and now take 4.3.  Each copy
 // costs the stream 10 to 20 us, so that chunks of 1 MB give 5.2 ms and of 256 KB
 // 11; 4 MB give 4.1, and 4 ms more when the slots are pinned on first use.
-// Under kSmall the gain is less than that first use costs.
+// Results under kSmall gain less than that first use costs.  Input has no fresh
+// pages, and the runtime's own copy keeps up with the threads for longer: builds
+// from 17 and 24 MB of reads took 1.10 and 1.53 ms with it and 1.14 and 1.53
+// with the slots, from 40 and 300 MB 2.7 and 20.3 against 2.4 and 16.7.
 class HostStage {
   public:
     struct Span {
@@ -153,7 +156,7 @@ class HostStage {
         void *dev;
         uint64_t bytes;
     };
-    static constexpr uint64_t kSmall = 16u << 20;
+    static constexpr uint64_t kSmall = 16u << 20, kSmallIn = 32u << 20;
 
     // All of the spans, in order of the stream.  Out: back when they have
     // arrived; in: back when the host's side has been read.
@@ -163,7 +166,7 @@ class HostStage {
             bytes += spans[i].bytes;
             chunks += (spans[i].bytes + kChunk - 1) / kChunk;
         }
-        if (bytes < kSmall || !reserve()) {
+        if (bytes < (out ? kSmall : kSmallIn) || !reserve()) {
             for (uint32_t i = 0; i < n; ++i) {
                 if (!spans[i].bytes) continue;
                 const hipError_t e = out ? hipMemcpyAsync(spans[i].host, spans[i].dev, spans[i].bytes, hipMemcpyDeviceToHost, s)
