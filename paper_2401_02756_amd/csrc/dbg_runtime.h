@@ -17,6 +17,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <thread>
 #include <vector>
 
@@ -149,6 +150,11 @@ class PinnedWord {
 // pages, and the runtime's own copy keeps up with the threads for longer: builds
 // from 17 and 24 MB of reads took 1.10 and 1.53 ms with it and 1.14 and 1.53
 // with the slots, from 40 and 300 MB 2.7 and 20.3 against 2.4 and 16.7.
+//
+// The slots belong to the process: a handle takes a set of them for the length
+// of one copy.  kIdle sets a device stay pinned between copies, as many as
+// threads are likely to copy at once, and none once the last handle that has
+// used any is destroyed.
 class HostStage {
   public:
     struct Span {
@@ -166,7 +172,8 @@ class HostStage {
             bytes += spans[i].bytes;
             chunks += (spans[i].bytes + kChunk - 1) / kChunk;
         }
-        if (bytes < (out ? kSmall : kSmallIn) || !reserve()) {
+        Slots *const slots = bytes < (out ? kSmall : kSmallIn) ? nullptr : take(device);
+        if (!slots) {
             for (uint32_t i = 0; i < n; ++i) {
                 if (!spans[i].bytes) continue;
                 const hipError_t e = out ? hipMemcpyAsync(spans[i].host, spans[i].dev, spans[i].bytes, hipMemcpyDeviceToHost, s)
@@ -181,9 +188,9 @@ class HostStage {
             hipError_t e = hipSetDevice(device);
             Piece held[2] = {};
             for (uint32_t slot = 0; e == hipSuccess && error.load(std::memory_order_relaxed) == hipSuccess; slot ^= 1) {
-                hipEvent_t ev = event_[2 * w + slot];
-                unsigned char *mine = pinned_.as<unsigned char>() + (2 * w + slot) * kChunk;
-                e = hipEventSynchronize(ev);  // what this slot last held, in an earlier call too, has arrived
+                hipEvent_t ev = slots->event[2 * w + slot];
+                unsigned char *mine = slots->pinned.as<unsigned char>() + (2 * w + slot) * kChunk;
+                e = hipEventSynchronize(ev);  // what this slot last held, in an earlier copy too, has arrived
                 if (out && e == hipSuccess && held[slot].bytes) std::memcpy(held[slot].host, mine, held[slot].bytes);
                 held[slot] = Piece{};
                 if (e != hipSuccess) break;
@@ -213,21 +220,29 @@ class HostStage {
         }
         const hipError_t e = static_cast<hipError_t>(error.load());
         if (e != hipSuccess) (void)hipStreamSynchronize(s);  // nothing still moves when the caller hears of it
+        give(slots);
         return e;
     }
     void release() {
-        for (auto &ev : event_) {
-            if (!ev) continue;
-            (void)hipEventSynchronize(ev);
-            (void)hipEventDestroy(ev);
-            ev = nullptr;
+        if (!counted_) return;
+        counted_ = false;
+        Slots *free = nullptr;
+        {
+            std::lock_guard<std::mutex> lock(pool().mu);
+            if (--pool().users == 0) std::swap(free, pool().idle);
         }
-        pinned_.release();
+        while (free) {
+            Slots *next = free->next;
+            free->release();
+            delete free;
+            free = next;
+        }
     }
 
+    static constexpr uint32_t kWorkers = 6, kIdle = 4;
+    static constexpr uint64_t kChunk = 2u << 20, kSlotBytes = 2 * kWorkers * kChunk;
+
   private:
-        static constexpr uint32_t kWorkers = 6;
-    static constexpr uint64_t kChunk = 2u << 20;
     struct Piece {
         unsigned char *host, *dev;
         uint64_t bytes;
@@ -242,14 +257,71 @@ class HostStage {
         }
         return {};
     }
-    bool reserve() {
-        if (pinned_.reserve(2 * kWorkers * kChunk) != hipSuccess) return false;
-        for (auto &ev : event_)
-            if (!ev && settled(hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return false;
-        return true;
+    struct Slots {  // two to a worker
+        HostBuf pinned;
+        hipEvent_t event[2 * kWorkers] = {};
+        int device = 0;
+        Slots *next = nullptr;
+        bool reserve() {
+            if (pinned.reserve(kSlotBytes) != hipSuccess) return false;
+            for (auto &ev : event)
+                if (settled(hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return false;
+            return true;
+        }
+        void release() {
+            for (auto &ev : event) {
+                if (!ev) continue;
+                (void)hipEventSynchronize(ev);
+                (void)hipEventDestroy(ev);
+            }
+            pinned.release();
+        }
+    };
+    struct Pool {
+        std::mutex mu;
+        Slots *idle = nullptr;
+        uint64_t users = 0;  // handles that have taken slots
+    };
+    static Pool &pool() {
+        static auto *p = new Pool;  // outlives the handles a program never closes
+        return *p;
     }
-    HostBuf pinned_;
-    hipEvent_t event_[2 * kWorkers] = {};
+    Slots *take(int device) {  // null: refused
+        {
+            std::lock_guard<std::mutex> lock(pool().mu);
+            if (!counted_) ++pool().users;
+            counted_ = true;
+            for (Slots **at = &pool().idle; *at; at = &(*at)->next)
+                if ((*at)->device == device) {
+                    Slots *s = *at;
+                    *at = s->next;
+                    return s;
+                }
+        }
+        Slots *s = new (std::nothrow) Slots;
+        if (s && !s->reserve()) {
+            s->release();
+            delete s;
+            s = nullptr;
+        }
+        if (s) s->device = device;
+        return s;
+    }
+    static void give(Slots *s) {
+        {
+            std::lock_guard<std::mutex> lock(pool().mu);
+            uint32_t n = 0;
+            for (const Slots *x = pool().idle; x; x = x->next) n += x->device == s->device;
+            if (n < kIdle) {
+                s->next = pool().idle;
+                pool().idle = s;
+                return;
+            }
+        }
+        s->release();
+        delete s;
+    }
+    bool counted_ = false;
 };
 
 // Makes `device` current for the scope of a call and restores the caller's.

@@ -9,6 +9,7 @@
 
 #include <cstdio>
 #include <deque>
+#include <map>
 #include <random>
 #include <vector>
 
@@ -19,26 +20,30 @@ struct Op {
     const void *from;
     size_t bytes;
 };
-struct Queue {
+struct State {
     std::deque<Op> ops;
     uint64_t pushed = 0, done = 0;
 };
+struct Queue {
+    std::shared_ptr<State> state = std::make_shared<State>();
+};
 struct Event {
-    Queue *q = nullptr;
+    std::shared_ptr<State> q;  // (an event outlives its stream)
     uint64_t upto = 0;
 };
 
 std::mutex mu;
 hipError_t last = hipSuccess;
 bool refuse_pinned = false, refuse_events = false;
-uint64_t pinned_calls = 0;
+uint64_t pinned_calls = 0, pinned_bytes = 0, pinned_most = 0;
+std::map<void *, size_t> pinned;
 
 hipError_t said(hipError_t e) {
     if (e != hipSuccess) last = e;
     return e;
 }
 
-void drain(Queue *q, uint64_t upto) {
+void drain(State *q, uint64_t upto) {
     while (q->done < upto) {
         const Op op = q->ops.front();
         q->ops.pop_front();
@@ -47,7 +52,7 @@ void drain(Queue *q, uint64_t upto) {
     }
 }
 
-Queue *queue(hipStream_t s) { return reinterpret_cast<Queue *>(s); }
+std::shared_ptr<State> &queue(hipStream_t s) { return reinterpret_cast<Queue *>(s)->state; }
 Event *event(hipEvent_t e) { return reinterpret_cast<Event *>(e); }
 
 }  // namespace
@@ -58,9 +63,15 @@ hipError_t hipHostMalloc(void **p, size_t bytes, unsigned int) {
     ++pinned_calls;
     if (refuse_pinned) return said(hipErrorOutOfMemory);
     *p = std::malloc(bytes);
+    pinned[*p] = bytes;
+    pinned_bytes += bytes;
+    pinned_most = std::max(pinned_most, pinned_bytes);
     return hipSuccess;
 }
 hipError_t hipHostFree(void *p) {
+    std::lock_guard<std::mutex> lock(mu);
+    pinned_bytes -= pinned[p];
+    pinned.erase(p);
     std::free(p);
     return hipSuccess;
 }
@@ -87,7 +98,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 }
 hipError_t hipEventSynchronize(hipEvent_t e) {
     std::lock_guard<std::mutex> lock(mu);
-    if (event(e)->q) drain(event(e)->q, event(e)->upto);
+    if (event(e)->q) drain(event(e)->q.get(), event(e)->upto);
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void *to, const void *from, size_t bytes, hipMemcpyKind, hipStream_t s) {
@@ -98,7 +109,7 @@ hipError_t hipMemcpyAsync(void *to, const void *from, size_t bytes, hipMemcpyKin
 }
 hipError_t hipStreamSynchronize(hipStream_t s) {
     std::lock_guard<std::mutex> lock(mu);
-    drain(queue(s), queue(s)->pushed);
+    drain(queue(s).get(), queue(s)->pushed);
     return hipSuccess;
 }
 hipError_t hipSetDevice(int) { return hipSuccess; }
@@ -127,12 +138,12 @@ static void round_trip(HostStage &stage, Queue &q, const std::vector<uint64_t> &
     std::vector<std::vector<unsigned char>> host, dev, back;
     std::vector<HostStage::Span> in, out;
     std::mt19937_64 rng(seed);
+    std::vector<uint64_t> block(5003);  // (a prime: no two chunks look alike)
+    for (auto &x : block) x = rng();
     for (const uint64_t n : sizes) {
         host.emplace_back(n);
-        for (size_t i = 0; i < n; i += 8) {
-            const uint64_t v = rng();
-            std::memcpy(host.back().data() + i, &v, std::min<size_t>(8, n - i));
-        }
+        for (size_t i = 0; i < n; i += 8 * block.size())
+            std::memcpy(host.back().data() + i, block.data(), std::min<size_t>(8 * block.size(), n - i));
         dev.emplace_back(n);
         back.emplace_back(n);
     }
@@ -196,6 +207,29 @@ static void check_refusals() {
     w.release();
 }
 
+// Many handles keep no more pinned memory than one, and none when all are gone.
+static void check_kept() {
+    const uint64_t before = pinned_bytes;  // a page of pinned words
+    std::vector<HostStage> stages(10);
+    Queue q;
+    pinned_most = 0;
+    for (size_t i = 0; i < stages.size(); ++i) round_trip(stages[i], q, {HostStage::kSmall + i}, i);
+    CHECK(pinned_most == before + HostStage::kSlotBytes, "%llu bytes pinned", (unsigned long long)(pinned_most - before));
+    std::vector<std::thread> threads;
+    for (size_t t = 0; t < 6; ++t)
+        threads.emplace_back([&, t] {
+            Queue own;
+            round_trip(stages[t], own, {HostStage::kSmall + 64 * t}, t);
+        });
+    for (auto &t : threads) t.join();
+    CHECK(pinned_bytes <= before + HostStage::kIdle * HostStage::kSlotBytes, "%llu bytes kept", (unsigned long long)(pinned_bytes - before));
+    for (auto &x : stages) x.release();
+    CHECK(pinned_bytes == before, "%llu bytes left", (unsigned long long)(pinned_bytes - before));
+    round_trip(stages[0], q, {HostStage::kSmall}, 5);  // and from the start again
+    stages[0].release();
+    CHECK(pinned_bytes == before, "%llu bytes left", (unsigned long long)(pinned_bytes - before));
+}
+
 static void check_threads() {
     std::vector<std::thread> threads;
     for (int t = 0; t < 3; ++t)
@@ -212,6 +246,7 @@ static void check_threads() {
 int main() {
     check_sizes();
     check_refusals();
+    check_kept();
     check_threads();
     if (failures) std::printf("%d failures\n", failures);
     else std::printf("ok\n");
