@@ -245,16 +245,47 @@ __device__ __forceinline__ uint32_t pack16(uint4 v, uint32_t *bad) {
     return pack4(v.x, bad) << 24 | pack4(v.y, bad) << 16 | pack4(v.z, bad) << 8 | pack4(v.w, bad);
 }
 
-// n <= 64 bases of ASCII from byte p on, as two packed words; *good is cleared
-// by a byte outside ACGTacgt.
-__device__ __noinline__ ulonglong2 ascii_bases128(const uint8_t *ascii, uint64_t p, uint32_t n, bool *good) {
-    uint64_t x[2] = {0, 0};
-    for (uint32_t i = 0; i < n; ++i) {
-        const uint32_t c = as_global(ascii)[p + i];
-        *good &= valid_letter(c);
-        x[i >> 5] |= (uint64_t)((c >> 1) & 3u) << (62 - 2 * (i & 31));
+// n <= 80 bases from byte p of the reads on, as packed words, sixteen bytes at a
+// time while these lie in the reads (len bytes); bad: a byte of the n outside
+// ACGTacgt.
+struct Bases {
+    uint64_t x[3];
+    bool bad;
+};
+using Bytes16 = uint32_t __attribute__((ext_vector_type(4), aligned(1), may_alias));
+
+__device__ __forceinline__ Bases ascii_bases(const uint8_t *ascii, uint64_t len, uint64_t p, uint32_t n) {
+    uint32_t v[6] = {0, 0, 0, 0, 0, 0};
+    bool good = true;
+#pragma unroll
+    for (uint32_t c = 0; c < 5; ++c) {
+        if (16 * c >= n) break;
+        const uint8_t *at = ascii + p + 16 * c;
+        uint32_t bad = 1;
+        if (p + 16 * c + 16 <= len) {
+            const Bytes16 q = *reinterpret_cast<const Bytes16 *>(at);
+            bad = 0;
+            v[c] = pack16(make_uint4(q.x, q.y, q.z, q.w), &bad);
+        }
+        if (bad) {  // the n bytes one by one (a byte behind them is not looked at)
+            v[c] = 0;
+            for (uint32_t i = 0; i < min(16u, n - 16 * c); ++i) {
+                good &= valid_letter(at[i]);
+                v[c] |= (((uint32_t)at[i] >> 1) & 3u) << (30 - 2 * i);
+            }
+        }
     }
-    return make_ulonglong2(x[0], x[1]);
+    return Bases{{(uint64_t)v[0] << 32 | v[1], (uint64_t)v[2] << 32 | v[3], (uint64_t)v[4] << 32}, !good};
+}
+
+// The read of window w, which starts it, behind read r (ws[r + 1] == w): the
+// last of those up to r1 that start at w, as reads shorter than k have no window.
+__device__ __forceinline__ uint64_t next_read(const uint64_t *__restrict__ ws, uint64_t r, uint64_t r1, uint64_t w) {
+    uint64_t step = 1;
+    for (++r; r + step <= r1 && ws[r + step] <= w; step *= 2) r += step;
+    for (; step; step /= 2)
+        if (r + step <= r1 && ws[r + step] <= w) r += step;
+    return r;
 }
 
 template <uint32_t RW>
@@ -370,9 +401,9 @@ __global__ __launch_bounds__(BLOCK) void k_sort_windows(const PassArgs *__restri
         tag[q] = d1 << RB;
     }
     const bool staged = fits && s_read[n_reads].x >= n_in;  // all the tile's bases, and the reads of all its windows
-    if (j0 < n_in) {
-        const uint32_t jend = min(j0 + PER, n_in);
-        if (staged) {
+    const uint32_t jend = min(j0 + PER, n_in);
+    if (staged) {
+        if (j0 < n_in) {
             uint32_t lo = 0, hi = n_reads;  // s_read[lo].x <= j0 < s_read[hi].x
             while (hi - lo > 1) {
                 const uint32_t mid = (lo + hi) >> 1;
@@ -424,23 +455,48 @@ __global__ __launch_bounds__(BLOCK) void k_sort_windows(const PassArgs *__restri
                     ++base;
                 }
             }
-        } else {  // more reads or bases than are staged: each window on its own, from the ASCII reads
-            bool good = true;
+        }
+    } else {
+        // More reads or bases than are staged: about two windows a read, or as many
+        // reads without one.  Each thread takes the reads of its own windows from
+        // the ASCII, and their records wait where the staging was.  Bound by the
+        // latency of a few loads a read.  A build from 4 M reads of exactly k = 31
+        // takes 0.40 ms (1.58 with each window found and decoded by itself, a byte at
+        // a time), of 10-50 bases at k = 45 0.39 (1.22), from 60 M of exactly 21 4.4
+        // (16.0).
+        static_assert(!WORDS && PER + 62 <= 80, "room for the records; bases of a thread's windows of one read");
+        R *s_rec = reinterpret_cast<R *>(s_room) + tid;
+        __syncthreads();  // s_read has been looked at
+        if (j0 < n_in) {
+            bool bad = false;
+            uint64_t w = w0 + j0, r = r0, hi = r1 + 1;  // ws[r] <= w < ws[hi]
+            while (hi - r > 1) {
+                const uint64_t mid = (r + hi) >> 1;
+                if (ws[mid] <= w) r = mid; else hi = mid;
+            }
+            uint64_t at = off[r] - off0 + (w - ws[r]);
+            for (uint32_t j = j0;;) {
+                const uint64_t z = ws[r + 1];  // the window that starts the next read
+                const uint32_t n = (uint32_t)min<uint64_t>(z - w, jend - j);
+                Bases x = ascii_bases(ascii, len, at, (uint32_t)min<uint64_t>(n + k - 1, z - w + k - 2));
+                bad |= x.bad;
+                for (uint32_t i = 0; i < n; ++i) {
+                    s_rec[(j++ - j0) * BLOCK] = record_of<RW>(x.x[0], x.x[1], k - 1, ++w == z ? 4u : 0u);
+                    x.x[0] = x.x[0] << 2 | x.x[1] >> 62;
+                    x.x[1] = x.x[1] << 2 | x.x[2] >> 62;
+                    x.x[2] <<= 2;
+                }
+                if (j == jend) break;
+                r = next_read(ws, r, r1, w);
+                at = off[r] - off0;
+            }
+            if (bad) atomic_or_u32(&st[i].err, kErrBase);
 #pragma unroll
             for (uint32_t q = 0; q < PER; ++q) {
-                const uint64_t w = w0 + j0 + q;
                 if (j0 + q >= n_in) break;
-                uint64_t lo = r0, hi = in.read_end;  // ws[lo] <= w < ws[hi]
-                while (hi - lo > 1) {
-                    const uint64_t mid = (lo + hi) >> 1;
-                    if (ws[mid] <= w) lo = mid; else hi = mid;
-                }
-                const bool sink = w + 1 == ws[lo + 1];
-                const ulonglong2 x = ascii_bases128(ascii, off[lo] - off0 + (w - ws[lo]), sink ? k - 1 : k, &good);
-                rec[q] = record_of<RW>(x.x, x.y, k - 1, sink ? 4u : 0u);
+                rec[q] = s_rec[q * BLOCK];
                 tag[q] = lds_add32(&s_cnt[bucket_of(image_top(RecOf<RW>::head(rec[q]) >> 3), d1)], 1u);
             }
-            if (!good) atomic_or_u32(&st[i].err, kErrBase);
         }
     }
     __syncthreads();
