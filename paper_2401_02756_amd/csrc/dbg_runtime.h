@@ -1012,20 +1012,29 @@ inline PassOpts opts_of(const dbg_graph *g) {
 // Segment geometry of a binned table of at least `cap` slots: d1 level-1
 // buckets of `fan` segments each (about the square root, so both partition
 // passes write runs of similar length), d1 * fan segments of kSegSlots slots
-// in all (a segment is a pair of digits of the key image).  A table of up to
-// `single` segments has one level: a bucket per segment.  False if the table
+// in all (a segment is a pair of digits of the key image).  False if the table
 // is too large for the two levels.
-inline bool binned_geometry(uint64_t cap, uint32_t *d1, uint32_t *fan, uint64_t *parts,
-                            uint64_t single = dbgk::kSingleParts) {
+inline bool binned_geometry(uint64_t cap, uint32_t *d1, uint32_t *fan, uint64_t *parts) {
     const uint64_t want = std::max<uint64_t>(1, (cap + dbgk::kSegSlots - 1) / dbgk::kSegSlots);
     uint64_t target = (uint64_t)std::ceil(std::sqrt((double)want));
-    if (want <= single) target = want;
     target = std::max<uint64_t>(1, std::min<uint64_t>(target, dbgk::kMaxD1));
     const uint64_t f = (want + target - 1) / target;
     if (f > dbgk::kMaxFan) return false;
     *fan = (uint32_t)f;
     *d1 = (uint32_t)((want + f - 1) / f);
     *parts = (uint64_t)*d1 * f;
+    return true;
+}
+
+// The same number of segments in one level, a bucket per segment, where the
+// table has up to kSingleParts of them and its build sorts tiles (the shaped
+// scatters are tuned to two levels).
+inline bool table_geometry(uint64_t cap, bool sorted, uint32_t *d1, uint32_t *fan, uint64_t *parts) {
+    if (!binned_geometry(cap, d1, fan, parts)) return false;
+    if (sorted && *parts <= dbgk::kSingleParts) {
+        *d1 = (uint32_t)*parts;
+        *fan = 1;
+    }
     return true;
 }
 
@@ -1056,9 +1065,7 @@ inline hipError_t order_after_zero(dbg_graph *g, hipStream_t s) {
 inline hipError_t allocate_table(dbg_graph *g, uint64_t cap) {
     if (g->binned) {
         uint64_t parts = 0;
-        // one level only where the partition takes it: the shaped scatters are tuned to two
-        const uint64_t single = g->bin_shape1 || g->bin_shape2 ? 0 : dbgk::kSingleParts;
-        if (!binned_geometry(cap, &g->d1, &g->fan, &parts, single)) return hipErrorInvalidValue;
+        if (!table_geometry(cap, !g->bin_shape1 && !g->bin_shape2, &g->d1, &g->fan, &parts)) return hipErrorInvalidValue;
         g->parts = (uint32_t)parts;
         cap = parts * dbgk::kSegSlots;
         hipError_t e;

@@ -101,7 +101,7 @@ extern "C" int dbg_build_device_static(dbg_graph *g, const uint8_t *d_reads, uin
     Instance two = hi[0];
     if (binned) {
         uint64_t parts = 0;
-        if (!binned_geometry(g->cap, &two.d1, &two.fan, &parts, 0)) return DBG_E_SCRATCH;
+        if (!binned_geometry(g->cap, &two.d1, &two.fan, &parts)) return DBG_E_SCRATCH;
         two.parts = (uint32_t)parts;
     }
     PassOpts shaped = o;

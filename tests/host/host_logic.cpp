@@ -46,6 +46,26 @@ static void check_geometry(uint64_t cap) {
     CHECK((uint64_t)d1 * (fan - 1) < want, "cap %llu: fan %u larger than needed", (unsigned long long)cap, fan);
 }
 
+// A table has the same slots whatever its build's route, and the geometry found
+// from its slots again is its own (dbg_build_device_static sizes by it).
+static void check_table_geometry() {
+    uint32_t d[3], f[3];
+    uint64_t p[3];
+    for (uint64_t s = 1; s <= 70000; s += s < 1100 ? 1 : 7) {
+        const uint64_t cap = s * dbgk::kSegSlots - s % 2;
+        CHECK(dbgrt::binned_geometry(cap, &d[0], &f[0], &p[0]) && dbgrt::table_geometry(cap, false, &d[1], &f[1], &p[1]) &&
+                  dbgrt::table_geometry(cap, true, &d[2], &f[2], &p[2]), "%llu segments refused", (unsigned long long)s);
+        CHECK(p[1] == p[0] && d[1] == d[0] && f[1] == f[0], "%llu segments: shaped", (unsigned long long)s);
+        CHECK(p[2] == p[0] && (uint64_t)d[2] * f[2] == p[2], "%llu segments: %llu in two levels, %llu", (unsigned long long)s,
+              (unsigned long long)p[0], (unsigned long long)p[2]);
+        CHECK((f[2] == 1 && d[2] <= dbgk::kSingleParts) || p[2] > dbgk::kSingleParts, "%llu segments: levels", (unsigned long long)s);
+        uint32_t d2, f2;
+        uint64_t p2;
+        CHECK(dbgrt::binned_geometry(p[2] * dbgk::kSegSlots, &d2, &f2, &p2) && p2 == p[0] && d2 == d[0] && f2 == f[0],
+              "%llu segments: not found again", (unsigned long long)s);
+    }
+}
+
 static void check_size_class() {
     uint64_t prev = 0;
     for (uint64_t x = 0; x < 300000; ++x) {
@@ -160,6 +180,7 @@ int main() {
             const int64_t segs = (int64_t)(s * s) + d;
             if (segs > 0) check_geometry((uint64_t)segs * dbgk::kSegSlots);
         }
+    check_table_geometry();
     check_size_class();
     std::mt19937_64 rng(20240105);
     check_host_counts(rng);

@@ -144,3 +144,17 @@ def test_batch_of_both_kinds():
             records.assert_exact((keys, counts * (rep + 1)), g.extract(), "set %d, build %d" % (j, rep))
     for g in gs:
         g.close()
+
+
+@pytest.mark.parametrize("want,slots", [(3, 4), (5, 6), (10, 12), (21, 25), (993, 1024)])
+def test_small_tables_round_up_as_large_ones(want, slots):
+    """A one-level table has the segments that two levels would give it, so that
+    an estimate which was just too low still fits."""
+    n = int(want * 2048 * 1.02) if want < 900 else int(want * 2048 * 0.9)
+    read = letters(n + K - 2)
+    rs = readsim.reads_from_strings([read], K)
+    print("[case] %d segments asked for, %d vertices" % (want, n), flush=True)
+    with dbg.Graph(capacity=want * 2048, flags=dbg.F_BINNED) as g:
+        assert g.stats()["capacity"] == slots * 2048
+        g.build(rs.reads, rs.offsets, K)
+        records.assert_exact(oracle.build_graph(rs.reads, rs.offsets, K), g.extract(), "capacity")
