@@ -765,6 +765,7 @@ struct Source {
     uint32_t pairs;        // pairs of units of a segment
     uint32_t per_unit;     // pieces of a unit
     uint32_t row_len, tile;  // offsets a row, records a tile
+    uint32_t rows;         // a segment's pieces are read in rows of 64 records, not in units
 };
 
 // A planned unit: consecutive pieces of one segment.
@@ -780,6 +781,17 @@ constexpr uint32_t kUnitRounds = 4;       // records a thread takes from a unit
 constexpr uint32_t kUnitRecords = kUnitRounds * kReduceBlock;  // a larger unit is read piece by piece
 constexpr uint32_t kUnitTarget = 1800;    // records a unit is meant to have at most
 constexpr uint32_t kStageUnits = 4;       // planned together
+
+// Few segments and many tiles (a small genome read deeply): a segment is many
+// pairs of units, and nothing of a pair's loads and planning hides behind a
+// write-back.  Where its pieces have kRowPiece records or more on average they
+// are read in rows of 64 instead, each wavefront its own, without a plan or a
+// barrier.  Bound by the latency of the LDS probes, of which a wavefront has one
+// row's under way.  ms of a reset and build, units / rows (count-and-scatter): 24 M
+// windows in 6 segments 9.3 / 7.2 (6.7), 122 M in 25 14.1 / 11.7 (11.6), in 56
+// 6.1 / 5.9 (5.7).  With shorter pieces a row's last lanes idle: 122 M in 110
+// 3.5 / 4.1, 48 sets in a batch 6.6 / 7.2.
+constexpr uint32_t kRowPiece = 128, kRowsAtOnce = 8;
 
 // The pass's end: the last workgroup to come here stores the statuses in the
 // host's memory (a copy command after the kernel takes longer).  Whole block.
@@ -889,7 +901,9 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
         S.gp1 = S.gp0 + (int32_t)width;
         const uint32_t most = min(kUnitPieces, max(1u, (uint32_t)((uint64_t)kUnitTarget * width / S.tile)));
         S.pairs = max(1u, (S.pieces + 2 * most - 1) / (2 * most));
-        S.per_unit = (S.pieces + 2 * S.pairs - 1) / (2 * S.pairs);
+        S.rows = S.pairs > 1 && width * kRowPiece <= S.tile;
+        if (S.rows) S.pairs = 1;
+        S.per_unit = S.rows ? S.pieces : (S.pieces + 2 * S.pairs - 1) / (2 * S.pairs);
         return S;
     };
     // The next stage: its pairs, and this wavefront's unit of it with this
@@ -943,6 +957,7 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
         const uint32_t n0 = oz[0] - oa[0], n1 = oz[1] - oa[1];
         const uint32_t inc = wave_scan(n0 + n1), p0 = inc - n0 - n1, p1 = inc - n1;
         mine.n = __builtin_amdgcn_readlane(inc, 63);
+        if (s_src[ns].rows) mine.n = wave & 1 ? 0u : ~0u;
         if (lane < Q) s_mark[wave][lane] = 0;
         __builtin_amdgcn_wave_barrier();
         if (mine.n <= kUnitRecords) {  // uniform
@@ -990,16 +1005,49 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
         }
     };
 
+    uint64_t my_claims = 0;  // this thread's in the segment
+    bool full = false;
+    // Pieces [s0, s1) of the workgroup's segment rel, read where they lie: rows of
+    // 64 records, numbered over 64 pieces at a time, every eighth to a wavefront.
+    const auto take_rows = [&](const Source &S, uint32_t rel, uint32_t s0, uint32_t s1) {
+        const uint16_t *o = as_global(S.off) + ((int32_t)rel - S.gp0);
+        const R *rec = reinterpret_cast<const R *>(as_global(S.rec));
+        for (uint32_t g = s0; g < s1; g += 64) {
+            uint32_t a = 0, n = 0;  // this lane's piece
+            if (g + lane < s1) {
+                a = o[(uint64_t)(g + lane) * S.row_len];
+                n = o[(uint64_t)(g + lane) * S.row_len + 1] - a;
+            }
+            const uint32_t inc = wave_scan((n + 63) / 64), first = inc - (n + 63) / 64;
+            const uint32_t total = __builtin_amdgcn_readlane(inc, 63);
+            for (uint32_t q0 = wave; q0 < total; q0 += kRowsAtOnce * kReduceWaves) {
+                R v[kRowsAtOnce];
+                uint32_t left[kRowsAtOnce];  // records of the piece from the row on
+#pragma unroll
+                for (uint32_t c = 0; c < kRowsAtOnce; ++c) {
+                    const uint32_t q = q0 + c * kReduceWaves;
+                    const uint64_t at = __ballot(first <= q && q < inc);  // none past the last row
+                    const uint32_t piece = at ? (uint32_t)__builtin_ctzll(at) : 0u;
+                    const uint32_t r = (q - __builtin_amdgcn_readlane(first, piece)) * 64;
+                    left[c] = at ? (uint32_t)__builtin_amdgcn_readlane(n, piece) - r : 0u;
+                    const uint64_t to = (uint64_t)(g + piece) * S.tile + __builtin_amdgcn_readlane(a, piece) + r;
+                    v[c] = lane < left[c] ? rec[to + lane] : RecOf<RW>::none();
+                }
+#pragma unroll
+                for (uint32_t c = 0; c < kRowsAtOnce; ++c)
+                    if (lane < left[c] && !reduce_record<STATS>(v[c], s_key, s_cnt, my_claims, home_mask, ps)) full = true;
+            }
+        }
+    };
+
     uint32_t cur_inst = m == 1 ? 0u : (uint32_t)last_le(m, gp0, [&](uint64_t j) { return inst[j].part_base; });
     uint64_t next_base = cur_inst + 1 < m ? inst[cur_inst + 1].part_base : ~0ull;
     bool skip = skipped(cur_inst);
     uint64_t *const xkeys = args->xkeys;
     uint32_t *const xcounts = args->xcounts;
     const uint64_t xcap = args->xcap;
-    uint64_t my_claims = 0;    // this thread's in the segment
     uint64_t inst_claims = 0;  // thread 0: the block's of cur_inst, not yet flushed
     uint32_t n_old = 0;        // vertices that the segment held before
-    bool full = false;
     next_stage();
     plan_unit();
     __syncthreads();
@@ -1039,21 +1087,9 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
                     !reduce_record<STATS>(rv[c], s_key, s_cnt, my_claims, home_mask, ps))
                     full = true;
             if (max(s_unit[2 * x].n, s_unit[2 * x + 1].n) > kUnitRecords) {
-                // long pieces: read where they lie, by the block or (shorter ones) by a wavefront each
                 const Source &S = s_src[cs];
-                for (uint32_t u = 2 * x; u < 2 * x + 2; ++u) {
-                    if (s_unit[u].n <= kUnitRecords) continue;
-                    const bool whole = s_unit[u].n > 256u * S.per_unit;
-                    const uint32_t step = whole ? 1u : kReduceWaves, width = whole ? kReduceBlock : 64u;
-                    const uint32_t s0 = s_unit[u].first, s1 = min(s0 + S.per_unit, S.pieces);
-                    for (uint32_t s = s0 + (whole ? 0u : wave); s < s1; s += step) {
-                        const uint16_t *o = as_global(S.off) + (uint64_t)s * S.row_len + ((int32_t)rel - S.gp0);
-                        const uint32_t a = o[0], z = o[1];
-                        const R *rec = reinterpret_cast<const R *>(as_global(S.rec)) + (uint64_t)s * S.tile;
-                        for (uint32_t r = a + (whole ? tid : lane); r < z; r += width)
-                            if (!reduce_record<STATS>(rec[r], s_key, s_cnt, my_claims, home_mask, ps)) full = true;
-                    }
-                }
+                for (uint32_t u = 2 * x; u < 2 * x + 2; ++u)
+                    if (s_unit[u].n > kUnitRecords) take_rows(S, rel, s_unit[u].first, min(s_unit[u].first + S.per_unit, S.pieces));
             }
             if (full) {
                 atomic_or_u32(&st[cur_inst].err, kErrFull);

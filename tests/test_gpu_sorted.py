@@ -158,3 +158,37 @@ def test_small_tables_round_up_as_large_ones(want, slots):
         assert g.stats()["capacity"] == slots * 2048
         g.build(rs.reads, rs.offsets, K)
         records.assert_exact(oracle.build_graph(rs.reads, rs.offsets, K), g.extract(), "capacity")
+
+
+@pytest.mark.parametrize("segments", [1, 2, 6, 25, 56, 110])
+@pytest.mark.parametrize("k", [21, 45])
+def test_few_segments_read_deeply(k, segments):
+    """Many tiles over few segments: long pieces are read in rows of 64 records
+    (up to 64 segments of one-word keys, 32 of two-word ones).  Built twice, the
+    second time into a table that holds the vertices."""
+    rng = np.random.default_rng([k, segments])
+    n = segments * 900
+    genome = letters(n + k)
+    reads = [genome]
+    for _ in range(22_000):
+        m = int(rng.integers(k - 3, 200))
+        at = int(rng.integers(0, max(1, n - m)))
+        reads.append(genome[at:at + m])
+    rs = readsim.reads_from_strings(reads, k)
+    for flags in (0, dbg.F_STATS):
+        print("[case] k=%d, %d segments, flags %d" % (k, segments, flags), flush=True)
+        with dbg.Graph(capacity=segments * 2048, flags=dbg.F_BINNED | flags) as g:
+            for rep in (1, 2):
+                g.build(rs.reads, rs.offsets, k)
+                if k > 32:
+                    hi, lo, counts = oracle.build_graph_wide(rs.reads, rs.offsets, k)
+                    keys, got = g.extract_sorted()
+                    keys = keys.reshape(-1, 2)
+                    assert np.array_equal(keys[:, 0], hi) and np.array_equal(keys[:, 1], lo)
+                    assert np.array_equal(got, rep * counts)
+                else:
+                    keys, counts = oracle.build_graph(rs.reads, rs.offsets, k)
+                    records.assert_exact((keys, counts * rep), g.extract(), "build %d" % rep)
+            if flags:
+                st = g.probe_stats()
+                assert st["cas_attempts"] - st["cas_lost"] == g.vertex_count() and st["lookups"] == g.stats()["windows"]
