@@ -790,7 +790,9 @@ constexpr uint32_t kStageUnits = 4;       // planned together
 // row's under way.  ms of a reset and build, units / rows (count-and-scatter): 24 M
 // windows in 6 segments 9.3 / 7.2 (6.7), 122 M in 25 14.1 / 11.7 (11.6), in 56
 // 6.1 / 5.9 (5.7).  With shorter pieces a row's last lanes idle: 122 M in 110
-// 3.5 / 4.1, 48 sets in a batch 6.6 / 7.2.
+// 3.5 / 4.1, 48 sets in a batch 6.6 / 7.2.  And where a workgroup has several
+// segments, others of its CU and its next segment's loads hide the stalls: 1.67 M
+// reads of 15-75 bases in 8300 segments 0.66 / 0.68.
 constexpr uint32_t kRowPiece = 128, kRowsAtOnce = 8;
 
 // The pass's end: the last workgroup to come here stores the statuses in the
@@ -901,7 +903,7 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
         S.gp1 = S.gp0 + (int32_t)width;
         const uint32_t most = min(kUnitPieces, max(1u, (uint32_t)((uint64_t)kUnitTarget * width / S.tile)));
         S.pairs = max(1u, (S.pieces + 2 * most - 1) / (2 * most));
-        S.rows = S.pairs > 1 && width * kRowPiece <= S.tile;
+        S.rows = S.pairs > 1 && per_block == 1 && width * kRowPiece <= S.tile;
         if (S.rows) S.pairs = 1;
         S.per_unit = S.rows ? S.pieces : (S.pieces + 2 * S.pairs - 1) / (2 * S.pairs);
         return S;
