@@ -763,6 +763,7 @@ struct Source {
     int32_t gp0, gp1;      // the run of segments (it may have begun before the workgroup's first)
     uint32_t pieces;       // of a segment
     uint32_t pairs;        // pairs of units of a segment
+    uint32_t units;        // units of a pair: 2, or 1 where a unit holds the segment
     uint32_t per_unit;     // pieces of a unit
     uint32_t row_len, tile;  // offsets a row, records a tile
     uint32_t rows;         // a segment's pieces are read in rows of 64 records, not in units
@@ -824,11 +825,14 @@ __device__ __forceinline__ void finish_pass(const PassArgs *args, const InstStat
 }
 static_assert(sizeof(InstStatus) % 8 == 0, "copied in words");
 
+using Offsets2 = uint32_t __attribute__((aligned(2), may_alias));  // two 16-bit offsets side by side
+
 // One workgroup per run of segments.  A segment's records are its pieces laid
 // end to end.  They are read in pairs of units, a unit being up to 128
 // consecutive pieces that a wavefront plans (a scan of the lengths, a bitmap of
 // the starts and a place per piece, as in k_sort_bucket); a segment of the
-// usual size is one pair, and a stage plans two pairs.  As nothing but LDS sits
+// usual size is one pair, and a stage plans two pairs; a segment of fewer records
+// is one unit, and a stage plans four.  As nothing but LDS sits
 // between a pair's records and the table, all of the next pair's records load
 // while a segment is written back, and the next stage's offsets load a stage
 // ahead; the planning itself goes where the write-back has its barriers anyway.
@@ -904,15 +908,18 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
         const uint32_t most = min(kUnitPieces, max(1u, (uint32_t)((uint64_t)kUnitTarget * width / S.tile)));
         S.pairs = max(1u, (S.pieces + 2 * most - 1) / (2 * most));
         S.rows = S.pairs > 1 && per_block == 1 && width * kRowPiece <= S.tile;
+        S.units = S.rows || S.pieces <= most ? 1u : 2u;
         if (S.rows) S.pairs = 1;
-        S.per_unit = S.rows ? S.pieces : (S.pieces + 2 * S.pairs - 1) / (2 * S.pairs);
+        S.per_unit = S.units == 1 ? S.pieces : (S.pieces + 2 * S.pairs - 1) / (2 * S.pairs);
         return S;
     };
     // The next stage: its pairs, and this wavefront's unit of it with this
-    // lane's two pieces (records [oa, oz) of their tiles).
-    uint32_t at = 0, at_pair = 0, cs = 0, ns = 0, next_pairs = 0;  // cs, ns: s_src slots of this stage and the next
+    // lane's two pieces: each one's first and last record in its tile, as they lie
+    // in the row of offsets.  They are taken apart when the unit is planned: that
+    // is where a wavefront is to wait for them, not here.
+    uint32_t at = 0, at_pair = 0, cs = 0, ns = 0, next_pairs = 0, next_units = 0;  // cs, ns: s_src slots of this stage and the next
     Unit mine{};
-    uint32_t oa[2] = {0, 0}, oz[2] = {0, 0};
+    uint32_t ow[2] = {0, 0};
     const auto next_stage = [&]() {
         next_pairs = 0;
         if (at >= n_gp) return;
@@ -925,22 +932,20 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
         __builtin_amdgcn_wave_barrier();
         const Source &S = s_src[ns];
         const uint32_t pairs = S.pairs, left = min((uint32_t)S.gp1, n_gp) - at;
-        next_pairs = min(kStageUnits / 2, pairs == 1 ? left : pairs - at_pair);
-        oa[0] = oa[1] = oz[0] = oz[1] = 0;
-        if (wave < 2 * next_pairs) {
-            const uint32_t x = wave >> 1, pair = pairs == 1 ? 0u : at_pair + x;
+        next_units = S.units;
+        next_pairs = min(kStageUnits >> (next_units - 1), pairs == 1 ? left : pairs - at_pair);
+        ow[0] = ow[1] = 0;
+        if (wave < next_units * next_pairs) {
+            const uint32_t x = wave >> (next_units - 1), pair = pairs == 1 ? 0u : at_pair + x;
             mine.gp = pairs == 1 ? at + x : at;
             mine.last = pair + 1 == pairs;
-            mine.first = (2 * pair + (wave & 1)) * S.per_unit;
+            mine.first = (next_units * pair + (wave & (next_units - 1))) * S.per_unit;
             mine.rec = S.rec + (uint64_t)mine.first * S.tile * RW;
             const uint16_t *o = as_global(S.off) + ((int32_t)mine.gp - S.gp0);
 #pragma unroll
             for (uint32_t h = 0; h < 2; ++h) {
                 const uint32_t p = 2 * lane + h, s = mine.first + p;
-                if (p < S.per_unit && s < S.pieces) {
-                    oa[h] = o[(uint64_t)s * S.row_len];
-                    oz[h] = o[(uint64_t)s * S.row_len + 1];
-                }
+                if (p < S.per_unit && s < S.pieces) ow[h] = *reinterpret_cast<const Offsets2 *>(o + (uint64_t)s * S.row_len);
             }
         }
         if (pairs == 1) {
@@ -955,11 +960,13 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
     };
     // plan this wavefront's unit of the next stage
     const auto plan_unit = [&]() {
-        if (wave >= 2 * next_pairs) return;
-        const uint32_t n0 = oz[0] - oa[0], n1 = oz[1] - oa[1];
+        if (wave >= next_units * next_pairs) return;
+        asm volatile("" : "+v"(ow[0]), "+v"(ow[1]));  // nothing of this is moved up to the loads
+        const uint32_t oa[2] = {ow[0] & 0xffffu, ow[1] & 0xffffu};
+        const uint32_t n0 = (ow[0] >> 16) - oa[0], n1 = (ow[1] >> 16) - oa[1];
         const uint32_t inc = wave_scan(n0 + n1), p0 = inc - n0 - n1, p1 = inc - n1;
         mine.n = __builtin_amdgcn_readlane(inc, 63);
-        if (s_src[ns].rows) mine.n = wave & 1 ? 0u : ~0u;
+        if (s_src[ns].rows) mine.n = ~0u;
         if (lane < Q) s_mark[wave][lane] = 0;
         __builtin_amdgcn_wave_barrier();
         if (mine.n <= kUnitRecords) {  // uniform
@@ -988,19 +995,26 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
     // end at a place that is always there, so that they follow each other.
     R rv[2 * kUnitRounds];
     uint32_t n_rv[2] = {0, 0};
-    const auto load_pair = [&](uint32_t x) {
+    const auto load_pair = [&](uint32_t units, uint32_t x) {
 #pragma unroll
         for (uint32_t h = 0; h < 2; ++h) {
             const R *src[kUnitRounds];
-            const uint32_t u = 2 * x + h;
-            n_rv[h] = s_unit[u].n <= kUnitRecords ? s_unit[u].n : 0u;
+            const uint32_t u = units * x + (h < units ? h : 0);
+            n_rv[h] = __builtin_amdgcn_readfirstlane(h < units && s_unit[u].n <= kUnitRecords ? s_unit[u].n : 0u);
             const R *rec = reinterpret_cast<const R *>(as_global(s_unit[u].rec));
-#pragma unroll
-            for (uint32_t c = 0; c < kUnitRounds; ++c) {
+            const auto find = [&](uint32_t c) {
                 const uint32_t q = c * kReduceWaves + wave, r = q * 64 + lane;
                 const uint32_t upto = s_base[u][q] + (uint32_t)__popcll(s_mark[u][q] & (~0ull >> (63 - lane)));
                 const uint32_t to = s_piece[u][(upto - 1) & (kUnitPieces - 1)] + r;
-                src[c] = r < n_rv[h] ? rec + to : reinterpret_cast<const R *>(rec1w);
+                if (r < n_rv[h]) src[c] = rec + to;
+            };
+#pragma unroll
+            for (uint32_t c = 0; c < kUnitRounds; ++c) src[c] = reinterpret_cast<const R *>(rec1w);
+            if (n_rv[h] > kReduceBlock) {
+#pragma unroll
+                for (uint32_t c = 0; c < kUnitRounds; ++c) find(c);
+            } else if (n_rv[h]) {
+                find(0);
             }
 #pragma unroll
             for (uint32_t c = 0; c < kUnitRounds; ++c) rv[h * kUnitRounds + c] = *src[c];
@@ -1053,17 +1067,17 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
     next_stage();
     plan_unit();
     __syncthreads();
-    load_pair(0);
+    load_pair(next_units, 0);
     for (;;) {  // stages
-        const uint32_t pairs = next_pairs;
+        const uint32_t pairs = next_pairs, units = next_units;
         cs = ns;
         next_stage();
         for (uint32_t x = 0; x < pairs; ++x) {
             const bool stage_end = x + 1 == pairs;
-            const uint32_t rel = s_unit[2 * x].gp;
-            const bool seg_end = s_unit[2 * x].last != 0;
+            const uint32_t u0 = units * x, rel = s_unit[u0].gp;
+            const bool seg_end = s_unit[u0].last != 0;
             const uint64_t gp = gp0 + rel;
-            if (s_unit[2 * x].first == 0) {  // a segment starts
+            if (s_unit[u0].first == 0) {  // a segment starts
                 if (gp >= next_base) {  // uniform: the run enters the next instance
                     if (tid == 0 && inst_claims) atomic_add_u64(&st[cur_inst].claimed, inst_claims);
                     inst_claims = 0;
@@ -1083,14 +1097,22 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
                     __syncthreads();
                 }
             }
-#pragma unroll
-            for (uint32_t c = 0; c < 2 * kUnitRounds; ++c)
+            const auto take = [&](uint32_t c) {
                 if (((c % kUnitRounds) * kReduceWaves + wave) * 64 + lane < n_rv[c / kUnitRounds] &&
                     !reduce_record<STATS>(rv[c], s_key, s_cnt, my_claims, home_mask, ps))
                     full = true;
-            if (max(s_unit[2 * x].n, s_unit[2 * x + 1].n) > kUnitRecords) {
+            };
+#pragma unroll
+            for (uint32_t h = 0; h < 2; ++h) {
+                if (!n_rv[h]) continue;  // uniform, as is the next: a sparse segment is a round of instructions, not eight
+                take(h * kUnitRounds);
+                if (n_rv[h] <= kReduceBlock) continue;
+#pragma unroll
+                for (uint32_t c = 1; c < kUnitRounds; ++c) take(h * kUnitRounds + c);
+            }
+            if (max(s_unit[u0].n, s_unit[u0 + units - 1].n) > kUnitRecords) {
                 const Source &S = s_src[cs];
-                for (uint32_t u = 2 * x; u < 2 * x + 2; ++u)
+                for (uint32_t u = u0; u < u0 + units; ++u)
                     if (s_unit[u].n > kUnitRecords) take_rows(S, rel, s_unit[u].first, min(s_unit[u].first + S.per_unit, S.pieces));
             }
             if (full) {
@@ -1118,7 +1140,7 @@ __global__ __launch_bounds__(kReduceBlock) __attribute__((amdgpu_waves_per_eu(RW
                 plan_unit();
                 __syncthreads();
             }
-            load_pair(stage_end ? 0 : x + 1);  // (after the last pair: a stale plan's, not used)
+            load_pair(stage_end ? next_units : units, stage_end ? 0 : x + 1);  // (after the last pair: a stale plan's, not used)
             if (!seg_end) continue;
             const uint32_t occupied = seg_count_slots(s_key, lane, wave);
             if (lane == 0) s_wave_n[wave] = occupied;

@@ -192,3 +192,36 @@ def test_few_segments_read_deeply(k, segments):
             if flags:
                 st = g.probe_stats()
                 assert st["cas_attempts"] - st["cas_lost"] == g.vertex_count() and st["lookups"] == g.stats()["windows"]
+
+
+@pytest.mark.parametrize("windows", [0.3, 3, 40, 700, 1700, 2600])
+@pytest.mark.parametrize("k", [21, 45])
+@pytest.mark.parametrize("vertices", [ONE_LEVEL, TWO_LEVEL], ids=["one-level", "two-level"])
+def test_segments_of_few_records(vertices, k, windows):
+    """From nearly empty segments, planned four together, to those of two units;
+    the second part is added to what the first left in them."""
+    total = int(windows * -(-2 * vertices // 2048))
+    rng = np.random.default_rng([vertices, k, total])
+    genome = letters(max(k + 50, min(total, vertices) // 2))
+    parts = []
+    for _ in range(2):
+        reads, left = [], total
+        while left > 0:
+            n = int(rng.integers(2, 120))
+            at = int(rng.integers(0, len(genome) - k))
+            reads.append(genome[at:at + min(n, left) + k - 2])
+            left -= n
+        parts.append(reads)
+    first, both = (readsim.reads_from_strings(p, k) for p in (parts[0], parts[0] + parts[1]))
+    second = readsim.reads_from_strings(parts[1], k)
+    print("[case] k=%d, %d vertices, %g windows a segment" % (k, vertices, windows), flush=True)
+    with dbg.Graph(expected_vertices=vertices, flags=dbg.F_BINNED) as g:
+        for new, rs in ((first, first), (second, both)):
+            g.build(new.reads, new.offsets, k)
+            if k > 32:
+                hi, lo, counts = oracle.build_graph_wide(rs.reads, rs.offsets, k)
+                keys, got = g.extract_sorted()
+                keys = keys.reshape(-1, 2)
+                assert np.array_equal(keys[:, 0], hi) and np.array_equal(keys[:, 1], lo) and np.array_equal(got, counts)
+            else:
+                records.assert_exact(oracle.build_graph(rs.reads, rs.offsets, k), g.extract(), "build")
