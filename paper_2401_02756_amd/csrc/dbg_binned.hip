@@ -1202,6 +1202,46 @@ __global__ __launch_bounds__(kExtractSegBlock) void k_extract_sums(const uint32_
     flush_block_sum(v, sums + blockIdx.x, &s_sum);
 }
 
+// A vertex on its way from its segment's entry e to record idx of the output.
+template <uint32_t EW, uint32_t RW>
+struct Vertex {
+    uint64_t key, low;
+    uint4 cnt;
+    __device__ __forceinline__ void load(const uint64_t *__restrict__ seg, uint32_t e) {
+        key = seg[e];
+        if constexpr (RW == 2) low = seg[kSegSlots + e];
+        cnt = seg_counts<RW>(seg)[e];
+    }
+    __device__ __forceinline__ void store(uint64_t *__restrict__ okeys, uint32_t *__restrict__ ocnt, uint64_t idx) const {
+        if constexpr (RW == 1) {
+            okeys[idx] = key_of_image(key & ~kOccupied);
+        } else {  // two key words per record: K >> 64, K mod 2^64
+            uint64_t kh, kl;
+            wide_key(key & ~kOccupied, low, kh, kl);
+            okeys[2 * idx] = kh;
+            okeys[2 * idx + 1] = kl;
+        }
+        *reinterpret_cast<uint4 *>(ocnt + 4 * idx) = cnt;
+    }
+};
+
+// Vertices of the segments before gp, by groups of kExtractGroup where there are
+// sums.  Whole block; a barrier.
+__device__ __forceinline__ uint64_t vertices_before(uint32_t gp, const uint32_t *__restrict__ seg_count,
+                                                    const uint64_t *__restrict__ sums) {
+    __shared__ uint64_t s_wave[kExtractSegBlock / 64];
+    uint64_t base = 0;
+    const uint32_t groups = sums ? gp / kExtractGroup : 0;
+    for (uint32_t i = threadIdx.x; i < groups; i += kExtractSegBlock) base += sums[i];
+    for (uint32_t i = groups * kExtractGroup + threadIdx.x; i < gp; i += kExtractSegBlock) base += seg_count[i];
+    for (int d = 32; d >= 1; d >>= 1) base += __shfl_xor(base, d, 64);
+    if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = base;
+    __syncthreads();
+    base = 0;
+    for (uint32_t w = 0; w < kExtractSegBlock / 64; ++w) base += s_wave[w];
+    return base;
+}
+
 // One workgroup per segment: its vertices (packed at its first entries) go
 // behind those of all segments before it, which the workgroup counts itself, by
 // groups where there are more segments than one (sums).  The last stores the
@@ -1218,47 +1258,63 @@ __global__ __launch_bounds__(kExtractSegBlock) void k_extract_seg(const uint64_t
                                                                   uint64_t *__restrict__ okeys,
                                                                   uint32_t *__restrict__ ocnt, uint64_t ocap,
                                                                   uint64_t *out_n) {
-    __shared__ uint64_t s_wave[kExtractSegBlock / 64];
     const uint32_t gp = blockIdx.x, n_all = seg_count[gp];
-    uint64_t base = 0;
-    const uint32_t groups = sums ? gp / kExtractGroup : 0;
-    for (uint32_t i = threadIdx.x; i < groups; i += kExtractSegBlock) base += sums[i];
-    for (uint32_t i = groups * kExtractGroup + threadIdx.x; i < gp; i += kExtractSegBlock) base += seg_count[i];
-    for (int d = 32; d >= 1; d >>= 1) base += __shfl_xor(base, d, 64);
-    if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = base;
-    __syncthreads();
-    base = 0;
-    for (uint32_t w = 0; w < kExtractSegBlock / 64; ++w) base += s_wave[w];
+    const uint64_t base = vertices_before(gp, seg_count, sums);
     const uint64_t *seg = table + (uint64_t)gp * kSegSlots * EW;
     const uint32_t n = (uint32_t)min<uint64_t>(min(n_all, kSegSlots), ocap > base ? ocap - base : 0);
     for (uint32_t e0 = threadIdx.x; e0 < n; e0 += kExtractUnroll * kExtractSegBlock) {
-        uint64_t key[kExtractUnroll], low[kExtractUnroll];
-        uint4 cnt[kExtractUnroll];
+        Vertex<EW, RW> v[kExtractUnroll];
 #pragma unroll
-        for (uint32_t i = 0; i < kExtractUnroll; ++i) {
-            const uint32_t e = min(e0 + i * kExtractSegBlock, n - 1);
-            key[i] = seg[e];
-            if constexpr (RW == 2) low[i] = seg[kSegSlots + e];
-            cnt[i] = seg_counts<RW>(seg)[e];
-        }
+        for (uint32_t i = 0; i < kExtractUnroll; ++i) v[i].load(seg, min(e0 + i * kExtractSegBlock, n - 1));
 #pragma unroll
         for (uint32_t i = 0; i < kExtractUnroll; ++i) {
             const uint32_t e = e0 + i * kExtractSegBlock;
             if (e >= n) break;
-            const uint64_t idx = base + e;
-            if constexpr (RW == 1) {
-                okeys[idx] = key_of_image(key[i] & ~kOccupied);
-            } else {  // two key words per record: K >> 64, K mod 2^64
-                uint64_t kh, kl;
-                wide_key(key[i] & ~kOccupied, low[i], kh, kl);
-                okeys[2 * idx] = kh;
-                okeys[2 * idx + 1] = kl;
-            }
-            *reinterpret_cast<uint4 *>(ocnt + 4 * idx) = cnt[i];
+            v[i].store(okeys, ocnt, base + e);
         }
     }
     if (gp + 1 == parts && threadIdx.x == 0) *out_n = base + n_all;
 }
+
+// The same for a table of many segments with few vertices in each: a workgroup
+// takes kFewSegs segments, whose vertices lie end to end in the output, and each
+// thread finds the segment of its vertex among them.
+constexpr uint32_t kFewSegs = 64, kFewVertices = 160;
+
+template <uint32_t EW, uint32_t RW>
+__global__ __launch_bounds__(kExtractSegBlock) void k_extract_few(const uint64_t *__restrict__ table, uint32_t parts,
+                                                                  const uint32_t *__restrict__ seg_count,
+                                                                  const uint64_t *__restrict__ sums,
+                                                                  uint64_t *__restrict__ okeys,
+                                                                  uint32_t *__restrict__ ocnt, uint64_t ocap,
+                                                                  uint64_t *out_n) {
+    __shared__ uint32_t s_first[kFewSegs + 1];
+    const uint32_t gp0 = blockIdx.x * kFewSegs, segs = min(kFewSegs, parts - gp0);
+    if (threadIdx.x < 64) {
+        const uint32_t n = threadIdx.x < segs ? min(seg_count[gp0 + threadIdx.x], kSegSlots) : 0u, inc = wave_scan(n);
+        s_first[threadIdx.x] = inc - n;
+        if (threadIdx.x == 63) s_first[kFewSegs] = inc;
+    }
+    const uint64_t base = vertices_before(gp0, seg_count, sums);
+    const uint32_t total = s_first[kFewSegs], n = (uint32_t)min<uint64_t>(total, ocap > base ? ocap - base : 0);
+    for (uint32_t j0 = threadIdx.x; j0 < n; j0 += kExtractUnroll * kExtractSegBlock) {
+        Vertex<EW, RW> v[kExtractUnroll];
+#pragma unroll
+        for (uint32_t i = 0; i < kExtractUnroll; ++i) {
+            const uint32_t j = min(j0 + i * kExtractSegBlock, n - 1);
+            const uint32_t s = (uint32_t)last_le(kFewSegs, j, [&](uint64_t x) { return s_first[x]; });
+            v[i].load(table + (uint64_t)(gp0 + s) * kSegSlots * EW, j - s_first[s]);
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < kExtractUnroll; ++i) {
+            const uint32_t j = j0 + i * kExtractSegBlock;
+            if (j >= n) break;
+            v[i].store(okeys, ocnt, base + j);
+        }
+    }
+    if (gp0 + segs == parts && threadIdx.x == 0) *out_n = base + total;
+}
+static_assert(kFewSegs == 64 && kExtractGroup % kFewSegs == 0, "a lane per segment");
 
 template <typename K>
 uint32_t occupancy_grid(K kernel, int device, uint32_t block, uint64_t cap, uint32_t dyn_lds) {
@@ -1546,16 +1602,20 @@ hipError_t launch_extract_binned(const uint64_t *table, uint32_t entry_words, ui
     else
         hipLaunchKernelGGL(k_extract_sums, dim3((parts + kExtractGroup - 1) / kExtractGroup), dim3(kExtractSegBlock), 0, s,
                            seg_count, parts, sums);
-    const dim3 g(parts), b(kExtractSegBlock);
-    if (key_words == 2)
-        hipLaunchKernelGGL((k_extract_seg<4, 2>), g, b, 0, s, table, parts, seg_count, sums, out_keys, out_counts,
-                           out_cap, out_n);
-    else if (entry_words == 4)
-        hipLaunchKernelGGL((k_extract_seg<4, 1>), g, b, 0, s, table, parts, seg_count, sums, out_keys, out_counts,
-                           out_cap, out_n);
-    else
-        hipLaunchKernelGGL((k_extract_seg<3, 1>), g, b, 0, s, table, parts, seg_count, sums, out_keys, out_counts,
-                           out_cap, out_n);
+    // A workgroup per segment costs 0.8 ns a segment, however few vertices it has; one
+    // for kFewSegs of them 0.15 us for each vertex a segment, as its threads go over
+    // them again, until the memory bounds both.  Segments x vertices, us: 1200 x 3 23
+    // against 25, 20 000 x 3 39 and 26, x 32 40 and 31, x 128 44 and 52, 200 000 x 3
+    // 189 and 35, x 128 320 and 237.
+    const bool few = sums && out_cap < (uint64_t)std::min(kFewVertices, parts / 512) * parts;  // out_cap: at most the vertices
+    const dim3 g(few ? (parts + kFewSegs - 1) / kFewSegs : parts), b(kExtractSegBlock);
+#define DBG_LAUNCH_EXTRACT(EW, RW)                                                                                     \
+    hipLaunchKernelGGL((few ? k_extract_few<EW, RW> : k_extract_seg<EW, RW>), g, b, 0, s, table, parts, seg_count, sums, \
+                       out_keys, out_counts, out_cap, out_n)
+    if (key_words == 2) DBG_LAUNCH_EXTRACT(4, 2);
+    else if (entry_words == 4) DBG_LAUNCH_EXTRACT(4, 1);
+    else DBG_LAUNCH_EXTRACT(3, 1);
+#undef DBG_LAUNCH_EXTRACT
     return hipGetLastError();
 }
 
