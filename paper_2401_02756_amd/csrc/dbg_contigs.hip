@@ -92,7 +92,11 @@ __device__ __forceinline__ uint64_t walk_find(const WalkTable &T, uint64_t key, 
     uint64_t s = home_slot(mix64(key), T.cap);
     for (uint64_t q = 0; q < T.cap; ++q) {
         const uint64_t cur = T.keys[s];
-        const uint32_t m = T.masks[s];  // beside the key, so that a step waits for one load, not two in a row
+        uint32_t m = 0;
+        if (next) {
+            m = T.masks[s];
+            asm volatile("" : "+v"(m));  // beside the key, not behind its comparison: a step waits for one load, not two in a row
+        }
         if (cur == tagv) {
             if (next) *next = next_of_mask(m);
             return s;
