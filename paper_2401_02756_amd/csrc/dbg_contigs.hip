@@ -23,6 +23,8 @@
 #include "dbg_runtime.h"
 #include "dbg_device.h"
 
+#include <type_traits>
+
 using namespace dbgrt;
 using dbgk::block_exclusive_scan;
 using dbgk::bucket_of;
@@ -277,28 +279,33 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk_length(WalkTable T, const u
         const uint64_t x1 = ((key0 << 2) | (it & 3)) & T.kmask;
         uint64_t hare = x1, tort = x1, power = 1, lam = 1, idx = 1, kept = 0;
         bool loop = false, bad = false;
-        for (;;) {
-            uint32_t next = kStops;
-            const uint64_t s = walk_find(T, hare, &next);
-            if (s == ~0ull || idx > limit) { bad = true; break; }
-            if (next == kStops) break;  // stops on x_idx
-            hare = succ(T, hare, next);
-            if (idx <= kKeep) {
-                kept |= (uint64_t)next << (2 * ((idx - 1) & 31));
-                if ((idx & 31) == 0) {
-                    keep[kKeepWords * i + (idx >> 5) - 1] = kept;
-                    kept = 0;
+        // false: the letters to keep are there, and the walk goes on
+        const auto follow = [&](auto keeps) {
+            for (;;) {
+                if (keeps && idx > kKeep) return false;
+                uint32_t next = kStops;
+                const uint64_t s = walk_find(T, hare, &next);
+                if (s == ~0ull || idx > limit) { bad = true; return true; }
+                if (next == kStops) return true;  // stops on x_idx
+                hare = succ(T, hare, next);
+                if (keeps) {
+                    kept |= (uint64_t)next << (2 * ((idx - 1) & 31));
+                    if ((idx & 31) == 0) {
+                        keep[kKeepWords * i + (idx >> 5) - 1] = kept;
+                        kept = 0;
+                    }
                 }
+                ++idx;
+                if (hare == tort) { loop = true; return true; }
+                if (power == lam) {
+                    tort = hare;
+                    power <<= 1;
+                    lam = 0;
+                }
+                ++lam;
             }
-            ++idx;
-            if (hare == tort) { loop = true; break; }
-            if (power == lam) {
-                tort = hare;
-                power <<= 1;
-                lam = 0;
-            }
-            ++lam;
-        }
+        };
+        if (!follow(std::true_type{})) follow(std::false_type{});  // a long walk's steps follow each other: nothing in them but the step
         if (idx <= kKeep) keep[kKeepWords * i + ((idx - 1) >> 5)] = kept;
         if (loop) {
             // x_{mu} is the first vertex of the loop: walk a from x1 and b from
@@ -398,13 +405,17 @@ __global__ __launch_bounds__(kWalkBlock) void k_walk_write(WalkTable T, const ui
             for (uint32_t b = 0; b < T.km1; ++b) *o++ = letter((uint32_t)(key0 >> (2 * (T.km1 - 1 - b))) & 3u);
             *o++ = letter((uint32_t)it & 3u);
             uint64_t cur = succ(T, key0, (uint32_t)it & 3u);
-            for (uint64_t e = 1; e < m; ++e) {
-                uint32_t c;
-                if (e <= kKeep) {
-                    if (e > 1 && ((e - 1) & 31) == 0) kept = keep[kKeepWords * i + ((e - 1) >> 5)];
-                    c = (uint32_t)kept & 3u;
-                    kept >>= 2;
-                } else if (walk_find(T, cur, &c) == ~0ull || c == kStops) {
+            uint64_t e = 1;
+            for (; e < min(m, (uint64_t)kKeep + 1); ++e) {
+                if (e > 1 && ((e - 1) & 31) == 0) kept = keep[kKeepWords * i + ((e - 1) >> 5)];
+                const uint32_t c = (uint32_t)kept & 3u;
+                kept >>= 2;
+                *o++ = letter(c);
+                cur = succ(T, cur, c);
+            }
+            for (; e < m; ++e) {
+                uint32_t c = kStops;
+                if (walk_find(T, cur, &c) == ~0ull || c == kStops) {
                     atomicOr(err, 8u);
                     break;
                 }
