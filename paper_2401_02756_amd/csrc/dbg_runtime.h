@@ -606,11 +606,13 @@ inline void fill_args(dbgk::PassArgs &a, const PassKey &k, const PassSizes &z, u
 // so a replay needs no kernel argument to change.
 struct Pass {
     DevBuf packed, ws, partials, tiles, dargs, dstatus;
+    // records of a binned pass, whichever way it partitions them
+    DevBuf rec1, rec2;
     // binned-mode scratch
-    DevBuf bplan, bbuckets, btotals, hist1, scan1, hist2, scan2, bpartials, rec1, rec2, pstart;
+    DevBuf bplan, bbuckets, btotals, hist1, scan1, hist2, scan2, bpartials, pstart;
     DevBuf tread1, tbucket2;
     // sorted-tile scratch
-    DevBuf splan, stotals, sbuckets, stile2, stread, soff1, soff2, sofft, sgsum, sgpre, srec1, srec2;
+    DevBuf splan, stotals, sbuckets, stile2, stread, soff1, soff2, sofft, sgsum, sgpre;
     HostBuf hargs, hstatus;  // pinned: PassArgs + Instance[m_cap]; InstStatus[m_cap] + CallState
     hipEvent_t ev_a = nullptr, ev_b = nullptr, ev_c = nullptr;
     hipEvent_t marks[dbgk::kBinMarks] = {};  // binned phase boundaries (timed, uncaptured)
@@ -653,7 +655,7 @@ struct Pass {
         DevBuf *d[] = {&packed, &ws, &partials, &tiles, &dargs, &dstatus, &bplan, &bbuckets,
                        &btotals, &hist1, &scan1, &hist2, &scan2, &bpartials, &rec1, &rec2, &pstart,
                        &tread1, &tbucket2, &splan, &stotals, &sbuckets, &stile2, &stread, &soff1, &soff2, &sofft,
-                       &sgsum, &sgpre, &srec1, &srec2};
+                       &sgsum, &sgpre};
         for (DevBuf *b : d) b->release();
         hargs.release();
         hstatus.release();
@@ -725,7 +727,7 @@ struct Pass {
             (e = grow(stread, z.tile_read)) != hipSuccess || (e = grow(soff1, z.off1)) != hipSuccess ||
             (e = grow(soff2, z.off2)) != hipSuccess || (e = grow(sofft, z.offt)) != hipSuccess ||
             (e = grow(sgsum, z.gsum)) != hipSuccess || (e = grow(sgpre, z.gpre)) != hipSuccess ||
-            (e = grow(srec1, z.rec1)) != hipSuccess || (e = grow(srec2, z.rec2)) != hipSuccess)
+            (e = grow(rec1, z.rec1)) != hipSuccess || (e = grow(rec2, z.rec2)) != hipSuccess)
             return e;
         sb.plan = splan.as<dbgk::SortPlan>();
         sb.totals = stotals.as<dbgk::SortTotals>();
@@ -737,8 +739,8 @@ struct Pass {
         sb.offt = sofft.as<uint32_t>();
         sb.gsum = sgsum.as<uint32_t>();
         sb.gpre = sgpre.as<uint64_t>();
-        sb.rec1 = srec1.as<uint64_t>();
-        sb.rec2 = srec2.as<uint64_t>();
+        sb.rec1 = rec1.as<uint64_t>();
+        sb.rec2 = rec2.as<uint64_t>();
         return hipSuccess;
     }
     std::vector<std::pair<PassKey, uint32_t>> sorted_memo;
