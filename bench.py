@@ -137,6 +137,13 @@ def binned_kernel_bytes(n_reads: int, total_bases: int, windows: int, vertices: 
                 scatter1=packed + 8 * windows, count2=8 * windows, scatter2=16 * windows, reduce=reduce_bytes)
 
 
+def partition(st: dict) -> dict:
+    """How the last binned pass partitioned its records (dbg_stats)."""
+    if st["sort_tiles"]:
+        return {"sorted_tiles": [x for x in (int(st["sort_tiles"]) & 0xffff, int(st["sort_tiles"]) >> 16) if x]}
+    return {"scatter_shapes": [int(st["bin_shape1"]), int(st["bin_shape2"])]}
+
+
 def scope_step_bytes(inserts: int, total_bases: int, capacity: int, vertices: int) -> int:
     """Bytes of one step under the hot-path scope table's model of the build:
     per k-mer an 8-byte key probe and a 4-byte counter add, the packed reads
@@ -658,7 +665,7 @@ def main() -> int:
                    "table_bytes": int(st["table_bytes"]), "load_factor": lf, "entry_bytes": st["entry_bytes"],
                    "mode": mode, "hip_graphs": graphs_on, "bin_chunks": shape["bin_chunks"],
                    "bin_scatter_div": shape["bin_scatter_div"],
-                   "bin_shapes": [int(st["bin_shape1"]), int(st["bin_shape2"])],
+                   "partition": partition(st),
                    "step": "reset + dbg_build_extract_device (build, every vertex written to device "
                            "buffers, status read back)"},
         "build_kernel_ginserts_s": round(rs.inserts / (r["kern_ms"] * 1e-3) / 1e9, 4),
@@ -704,7 +711,7 @@ def main() -> int:
         br = bl["r"]
         bac = {"workload": "plain build, %s" % b.meta["name"], "inserts_per_step": b.inserts,
                "vertices": br["V"], "capacity": br["cap"], "load_factor": blf, "mode": bmode,
-               "bin_shapes": [int(br["st"]["bin_shape1"]), int(br["st"]["bin_shape2"])],
+               "partition": partition(br["st"]),
                "value": round(br["value"], 4), "ms_per_step": round(br["ms_step"], 4),
                "build_kernel_ginserts_s": round(b.inserts / (br["kern_ms"] * 1e-3) / 1e9, 4),
                "roofline": bl["roofline"], "phases": bl["phases"]}

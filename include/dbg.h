@@ -164,10 +164,13 @@ typedef struct {
     uint64_t graph_captures;  /* build passes captured as graphs (DBG_F_GRAPH) */
     uint64_t graph_replays;   /* build passes replayed from a captured graph */
     uint32_t binned;          /* 1 if the graph uses the binned build */
-    uint32_t pad;
-    uint32_t bin_chunks;      /* binned launch shape in use (0 = defaults) */
+    uint32_t sort_tiles;      /* records of a sorted tile in the last binned pass: the first level's, and the
+                                 second's << 16 (0 there: one level); 0 if it counted and scattered, or before one */
+    uint32_t bin_chunks;      /* binned launch shape, as in dbg_config (0 = defaults) */
     uint32_t bin_scatter_div;
-    uint32_t bin_shape1;      /* scatter shapes of the last binned pass (as dbg_config; 0 before one) */
+    uint32_t bin_shape1;      /* scatter shapes of the last binned pass (as dbg_config; 0 before one).  A pass that
+                                 sorted tiles ran no scatter: these are then the shapes that counting and
+                                 scattering would have taken for the same table */
     uint32_t bin_shape2;
 } dbg_stats;
 

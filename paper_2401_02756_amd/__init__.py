@@ -84,7 +84,7 @@ class Stats(ctypes.Structure):
         ("graph_captures", ctypes.c_uint64),
         ("graph_replays", ctypes.c_uint64),
         ("binned", ctypes.c_uint32),
-        ("pad", ctypes.c_uint32),
+        ("sort_tiles", ctypes.c_uint32),
         ("bin_chunks", ctypes.c_uint32),
         ("bin_scatter_div", ctypes.c_uint32),
         ("bin_shape1", ctypes.c_uint32),

@@ -317,6 +317,7 @@ int dbg_get_stats(dbg_graph *g, dbg_stats *out) {
     out->graph_captures = g->pass.captures;
     out->graph_replays = g->pass.replays;
     out->binned = g->binned ? 1u : 0u;
+    out->sort_tiles = g->pass.sort_tiles;
     out->bin_chunks = g->bin_chunks;
     out->bin_scatter_div = g->bin_div;
     out->bin_shape1 = g->pass.shapes & 0xffu;

@@ -296,9 +296,10 @@ struct SortBuffers {    // device scratch of one pass
 // one more.
 constexpr uint32_t kDoneLines = 32, kDoneStride = 16, kDoneWords = (kDoneLines + 1) * kDoneStride;
 
-// The scatter shapes that dbg_stats reports for automatic shapes (code of the
-// first | second << 8): big tiles, of 128 KB in a first level of many buckets;
-// a first level of long keys counts as big only there.
+// The scatter shapes that dbg_stats reports for automatic shapes, which run no
+// scatter: those that the count-and-scatter partition takes for the same table
+// (code of the first | second << 8): big tiles, of 128 KB in a first level of
+// many buckets; a first level of long keys counts as big only there.
 constexpr uint32_t auto_shapes(uint32_t rec_words, uint32_t d1) {
     return (rec_words == 1 ? (d1 > 384 ? 4u : 3u) : (d1 > 384 ? 3u : 1u)) | 3u << 8;
 }

@@ -564,6 +564,7 @@ struct PassSizes {
 };
 
 inline PassOpts opts_of(const dbg_graph *g);
+inline uint32_t scatter_d1(const Instance *hi, uint32_t mm);
 
 // The argument block of a pass (PassArgs) for key k.
 inline void fill_args(dbgk::PassArgs &a, const PassKey &k, const PassSizes &z, uint32_t mm, const Instance *hi,
@@ -632,7 +633,8 @@ struct Pass {
     };
     std::vector<Cached> graphs;
     uint64_t captures = 0, replays = 0;
-    uint32_t shapes = 0;  // scatter shapes of the last binned pass, as dbg_stats reports them (shape + 1)
+    // of the last binned pass, as dbg_stats reports them: scatter shapes (shape + 1), records of a sorted tile by level
+    uint32_t shapes = 0, sort_tiles = 0;
 
     hipError_t init() {
         hipError_t e = hipEventCreate(&ev_a);
@@ -871,10 +873,12 @@ struct Pass {
         if (k.sorted) {
             sb.done = partials.as<uint64_t>() + dbgk::scan_words(k.n_cap);
             sorted_grids(k, device, sb);
-            shapes = dbgk::auto_shapes(k.rw, k.d1_cap);
+            shapes = dbgk::auto_shapes(k.rw, scatter_d1(hi, mm));
+            sort_tiles = sb.tile1 | (sb.two_level ? sb.tile2 << 16 : 0u);
         } else if (binned) {
             binned_grids(k, device, bb);
             shapes = (bb.shape1 + 1) | (bb.shape2 + 1) << 8;
+            sort_tiles = 0;
         }
         fill_args(*host_args(), k, z, mm, hi, d_reads, len, d_off, n, check_ends, xkeys, xcounts, xcap, o);
         host_args()->host_status = hstatus.as<InstStatus>();
@@ -1038,6 +1042,19 @@ inline bool table_geometry(uint64_t cap, bool sorted, uint32_t *d1, uint32_t *fa
         *fan = 1;
     }
     return true;
+}
+
+// Level-1 buckets that a count-and-scatter launch over these instances would
+// have, in the capacities of a pass: the two-level geometry's, whatever theirs is.
+inline uint32_t scatter_d1(const Instance *hi, uint32_t mm) {
+    uint32_t most = 1;
+    for (uint32_t i = 0; i < mm; ++i) {
+        uint32_t d1 = hi[i].d1, fan = 0;
+        uint64_t parts = 0;
+        if (hi[i].parts) (void)binned_geometry((uint64_t)hi[i].parts * dbgk::kSegSlots, &d1, &fan, &parts);
+        most = std::max(most, d1);
+    }
+    return (uint32_t)std::min<uint64_t>(size_class(most, 16), dbgk::kMaxD1);
 }
 
 // Zero the whole table on the graph's stream; builds on other streams are

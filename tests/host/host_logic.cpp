@@ -66,6 +66,29 @@ static void check_table_geometry() {
     }
 }
 
+// The scatter shapes that a pass by sorted tiles reports are those of the two
+// levels that the same table has in a count-and-scatter launch, also where its
+// own tables have one.
+static void check_reported_shapes() {
+    for (uint64_t s = 1; s <= 600000; s += s < 1100 ? 1 : 997) {
+        Instance one[2] = {}, two[2] = {};
+        uint64_t parts = 0;
+        for (int i = 0; i < 2; ++i) {
+            const uint64_t cap = (i ? s : s / 3 + 1) * dbgk::kSegSlots;
+            if (!dbgrt::table_geometry(cap, true, &one[i].d1, &one[i].fan, &parts)) return;
+            one[i].parts = (uint32_t)parts;
+            if (!dbgrt::binned_geometry(cap, &two[i].d1, &two[i].fan, &parts)) return;
+            two[i].parts = (uint32_t)parts;
+        }
+        uint32_t most = 1;
+        for (const Instance &x : two) most = std::max(most, x.d1);
+        const uint32_t d1 = (uint32_t)std::min<uint64_t>(dbgrt::size_class(most, 16), dbgk::kMaxD1);
+        CHECK(dbgrt::scatter_d1(one, 2) == d1, "%llu segments: %u, not %u", (unsigned long long)s, dbgrt::scatter_d1(one, 2), d1);
+        CHECK(dbgk::auto_shapes(1, dbgrt::scatter_d1(one, 2)) == (d1 > 384 ? 0x304u : 0x303u), "%llu segments", (unsigned long long)s);
+        CHECK(dbgk::auto_shapes(2, dbgrt::scatter_d1(one, 2)) == (d1 > 384 ? 0x303u : 0x301u), "%llu segments", (unsigned long long)s);
+    }
+}
+
 static void check_size_class() {
     uint64_t prev = 0;
     for (uint64_t x = 0; x < 300000; ++x) {
@@ -181,6 +204,7 @@ int main() {
             if (segs > 0) check_geometry((uint64_t)segs * dbgk::kSegSlots);
         }
     check_table_geometry();
+    check_reported_shapes();
     check_size_class();
     std::mt19937_64 rng(20240105);
     check_host_counts(rng);
