@@ -519,7 +519,7 @@ int dbg_autotune(int32_t device, uint32_t m, const uint64_t *read_begin, const u
                  const uint64_t *d_offsets, uint32_t keep_flags, uint32_t repeats, uint32_t tune_flags,
                  dbg_tuning *out);
 
-/* Every configuration the tuner's search may time, for the binned (binned
+/* The space that the tuner's search moves in, for the binned (binned
  * != 0) or the direct build: the cross product of its axes (load factor,
  * and binned chunks, scatter shapes (five pairs) and scatter divisor, or
  * direct block size, windows per thread and merging).  Writes min(cap, *n) entries (only the configuration

@@ -1,12 +1,12 @@
 // Autotuner: times complete builds of a calibration input under candidate
 // configurations and keeps the fastest.  The search is coordinate-wise:
-// binned mode over load factors, then over its partition launch shape
-// (chunks per workgroup, the scatter shapes, then the second scatter's grid
-// divisor); then
+// binned mode over load factors, then over its partition's scatter shapes (and,
+// with set shapes, their launch: dbg_tune.h); then
 // (unless binned mode is already far ahead) the direct build over launch
 // shapes, wavefront merging and load factors.  Choices are cached in the
 // process and in a cache file keyed by device model.
 #include "dbg_runtime.h"
+#include "dbg_tune.h"
 
 #include <sys/stat.h>
 
@@ -18,25 +18,6 @@
 using namespace dbgrt;
 
 namespace {
-
-struct Cand {
-    bool binned;
-    double lf;
-    uint32_t block, wpt;
-    bool merge;
-    uint32_t bin_chunks = 0, bin_div = 0, bin_shape1 = 0, bin_shape2 = 0;
-};
-
-// The axes of the search.
-constexpr double kLoadFactors[] = {0.5, 0.4, 0.6, 0.7};
-constexpr uint32_t kBinChunks[] = {0, 4, 8, 16, 64};  // 0: the default, 32
-constexpr uint32_t kBinDivs[] = {0, 1, 2, 4};         // 0: automatic
-// scatter shapes, first and second (dbg_config bin_shape1/2): automatic,
-// plain tiles, staged lines, big tiles, big tiles then staged lines, wide
-// big tiles then big tiles
-constexpr uint32_t kBinShapes[][2] = {{0, 0}, {1, 1}, {2, 2}, {3, 3}, {3, 2}, {4, 3}};
-constexpr uint32_t kBlocks[] = {256, 512, 1024};
-constexpr uint32_t kWpts[] = {2, 4, 8};
 
 struct Workload {
     int device;
@@ -290,38 +271,7 @@ int dbg_autotune(int32_t device, uint32_t m, const uint64_t *read_begin, const u
     };
 
     double binned_best = 1e300;
-    if (all_binnable) {
-        // load factor at the default launch shape, then the launch shape at the best load factor
-        Cand bc{true, 0.5, 256, 4, false};
-        for (double lf : kLoadFactors) {
-            const Cand c{true, lf, 256, 4, false};
-            const double ms = consider(c);
-            if (lf == 0.5) best.default_ms = ms;
-            if (ms < binned_best) binned_best = ms, bc = c;
-        }
-        for (uint32_t ch : kBinChunks) {
-            if (ch == 0) continue;
-            Cand c = bc;
-            c.bin_chunks = ch;
-            const double ms = consider(c);
-            if (ms < binned_best) binned_best = ms, bc = c;
-        }
-        for (const auto &sh : kBinShapes) {
-            if (sh[0] == 0 && sh[1] == 0) continue;
-            Cand c = bc;
-            c.bin_shape1 = sh[0];
-            c.bin_shape2 = sh[1];
-            const double ms = consider(c);
-            if (ms < binned_best) binned_best = ms, bc = c;
-        }
-        for (uint32_t dv : kBinDivs) {
-            if (dv == 0) continue;
-            Cand c = bc;
-            c.bin_div = dv;
-            const double ms = consider(c);
-            if (ms < binned_best) binned_best = ms, bc = c;
-        }
-    }
+    if (all_binnable) (void)search_binned(consider, &binned_best, &best.default_ms);
     // direct build: launch shape, then merging, then load factor
     Cand dc{false, 0.5, 256, 4, false};
     double dbest = consider(dc);

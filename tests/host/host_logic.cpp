@@ -4,6 +4,7 @@
 // validate and size its input.  Prints one line per failure and "ok" at the
 // end; the exit status is the number of failures (capped at 100).
 #include "dbg_runtime.h"
+#include "dbg_tune.h"
 
 #include <cmath>
 #include <cstdio>
@@ -63,6 +64,39 @@ static void check_table_geometry() {
         uint64_t p2;
         CHECK(dbgrt::binned_geometry(p[2] * dbgk::kSegSlots, &d2, &f2, &p2) && p2 == p[0] && d2 == d[0] && f2 == f[0],
               "%llu segments: not found again", (unsigned long long)s);
+    }
+}
+
+// The search times no build twice (with automatic shapes chunks and divisor do
+// nothing), finds the best of what it times, and tunes the scatter's launch where
+// set shapes are the best.
+static void check_tuner(std::mt19937_64 &rng) {
+    for (int round = 0; round < 400; ++round) {
+        std::vector<dbgrt::Cand> seen;
+        double least = 1e300, at_half = 0;
+        bool twice = false;
+        const int favour = round % 3;  // automatic shapes, set ones, neither
+        const auto consider = [&](const dbgrt::Cand &c) {
+            const bool shaped = c.bin_shape1 || c.bin_shape2;
+            for (const auto &x : seen)
+                twice |= x.lf == c.lf && x.bin_shape1 == c.bin_shape1 && x.bin_shape2 == c.bin_shape2 &&
+                         (!shaped || (x.bin_chunks == c.bin_chunks && x.bin_div == c.bin_div));
+            seen.push_back(c);
+            double ms = 1.0 + (double)(rng() % 1000) / 1000;
+            if (favour == 0 && !shaped) ms /= 4;
+            if (favour == 1 && shaped) ms /= 4;
+            if (rng() % 20 == 0) ms = 1e300;
+            least = std::min(least, ms);
+            if (seen.size() == 1) at_half = ms;
+            return ms;
+        };
+        double best_ms = 0, default_ms = 0;
+        const dbgrt::Cand best = dbgrt::search_binned(consider, &best_ms, &default_ms);
+        CHECK(!twice, "round %d: a build timed twice", round);
+        CHECK(best_ms == least && default_ms == at_half, "round %d: %g of %g", round, best_ms, least);
+        const bool shaped = best.bin_shape1 || best.bin_shape2;
+        CHECK(seen.size() == (shaped ? 16u : 9u) && (shaped || (!best.bin_chunks && !best.bin_div)), "round %d: %zu candidates",
+              round, seen.size());
     }
 }
 
@@ -209,6 +243,7 @@ int main() {
     std::mt19937_64 rng(20240105);
     check_host_counts(rng);
     check_chunks(rng);
+    check_tuner(rng);
     if (failures) std::printf("%d failures\n", failures);
     else std::printf("ok\n");
     return failures > 100 ? 100 : failures;
