@@ -510,7 +510,8 @@ typedef struct {
  * environment variable DBG_TUNE_CACHE, else
  * $XDG_CACHE_HOME/libdbg/autotune.tsv or $HOME/.cache/libdbg/autotune.tsv
  * (DBG_TUNE_CACHE set but empty: no file).  Lines are appended, the last
- * line of a key wins.
+ * line of a key wins; lines of an earlier library whose kernels were others
+ * are passed over.
  * k may exceed 32 (up to 64) only for m = 1; such a graph is tuned over the
  * direct build's launch shape and load factor.
  * Errors: DBG_E_INVAL, or the error of the default configuration's build. */

@@ -185,7 +185,8 @@ std::string cache_key(const Workload &w) {
         ev += w.expected ? w.expected[i] : 0;
     }
     char buf[160];
-    std::snprintf(buf, sizeof buf, "v3/%u/%llx/%d/%d/%d/%x", w.m, (unsigned long long)kmask,
+    // the version: of what was timed.  v4: automatic shapes sort tiles
+    std::snprintf(buf, sizeof buf, "v4/%u/%llx/%d/%d/%d/%x", w.m, (unsigned long long)kmask,
                   size_bucket(w.reads_len), size_bucket(w.read_begin[w.m]), size_bucket(ev), w.keep_flags);
     return device_model(w.device) + "/" + buf;
 }

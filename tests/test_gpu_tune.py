@@ -163,3 +163,24 @@ def test_tuning_persists_in_the_cache_file(tmp_path):
         assert first[key] == second[key], key
     lines = path.read_text().splitlines()
     assert len(lines) == 1 and "\t" in lines[0] and "gfx" in lines[0]
+
+
+def test_tunings_of_other_kernels_are_passed_over(tmp_path):
+    """A cached choice was timed with the library's kernels of its time: the
+    lines before automatic shapes sorted tiles are not taken up, however good."""
+    path = tmp_path / "autotune.tsv"
+    env = dict(os.environ, DBG_TUNE_CACHE=str(path))
+
+    def tune():
+        out = subprocess.run([sys.executable, "-c", _TUNE_CHILD, ROOT], env=env, capture_output=True, text=True,
+                             timeout=240, cwd=ROOT)
+        assert out.returncode == 0, out.stderr[-2000:]
+        return json.loads(out.stdout.strip().splitlines()[-1])
+
+    say("a line of the count-and-scatter kernels")
+    tune()
+    key = path.read_text().split("\t")[0]
+    old = "/".join("v3" if part in ("v3", "v4") else part for part in key.split("/"))
+    path.write_text(old + "\t0.4 8 0 0 16 2 3 3 0.000001 0.000002\n")
+    t = tune()
+    assert t["from_cache"] == 0 and t["candidates"] >= 4 and t["best_ms"] > 0.001
