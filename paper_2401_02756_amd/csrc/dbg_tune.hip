@@ -125,7 +125,7 @@ void load_cache_file() {
         unsigned flags = 0, block = 0, wpt = 0, chunks = 0, div = 0, sh1 = 0, sh2 = 0;
         if (std::sscanf(tab + 1, "%lf %u %u %u %u %u %u %u %lf %lf", &t.load_factor, &flags, &block, &wpt, &chunks,
                         &div, &sh1, &sh2, &t.best_ms, &t.default_ms) != 10 ||
-            sh1 > 3 || sh2 > 3)
+            sh1 > 4 || sh2 > 4)
             continue;
         if (!(t.load_factor > 0 && t.load_factor < 1) || (flags & ~(uint32_t)(DBG_F_BINNED | DBG_F_MERGE)))
             continue;

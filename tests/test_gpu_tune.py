@@ -184,3 +184,19 @@ def test_tunings_of_other_kernels_are_passed_over(tmp_path):
     path.write_text(old + "\t0.4 8 0 0 16 2 3 3 0.000001 0.000002\n")
     t = tune()
     assert t["from_cache"] == 0 and t["candidates"] >= 4 and t["best_ms"] > 0.001
+
+
+def test_every_choice_is_read_back(tmp_path):
+    """A cached choice of the wide big tiles (shape 4) is one of the search's, too."""
+    path = tmp_path / "autotune.tsv"
+    env = dict(os.environ, DBG_TUNE_CACHE=str(path))
+    runs = []
+    for i in range(2):
+        say("shapes 4 and 3, process %d" % i)
+        out = subprocess.run([sys.executable, "-c", _TUNE_CHILD, ROOT], env=env, capture_output=True, text=True,
+                             timeout=240, cwd=ROOT)
+        assert out.returncode == 0, out.stderr[-2000:]
+        runs.append(json.loads(out.stdout.strip().splitlines()[-1]))
+        key = path.read_text().split("\t")[0]
+        path.write_text(key + "\t0.4 8 0 0 16 2 4 3 0.5 0.75\n")
+    assert runs[1]["from_cache"] == 2 and (runs[1]["bin_shape1"], runs[1]["bin_shape2"]) == (4, 3)
