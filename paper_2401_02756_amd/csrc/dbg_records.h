@@ -291,6 +291,9 @@ __device__ __forceinline__ uint32_t seg_count_slots(const uint64_t *s_key, uint3
     return mine;
 }
 
+// Two key words of the caller's, whose array may start at any word.
+using Keys2 = uint64_t __attribute__((ext_vector_type(2), aligned(8)));
+
 // Write this wavefront's occupied slots to the table's segment, packed, and
 // zero them; with xkeys also, as keys and counters, to the caller's arrays from
 // xbase on, which the caller has reserved for the whole segment.  s_wave_n:
@@ -328,7 +331,7 @@ __device__ __forceinline__ uint32_t seg_store(uint64_t *seg, uint64_t *s_key, ui
                 } else {  // two key words per record: K >> 64, K mod 2^64
                     uint64_t kh, kl;
                     wide_key(tagv & ~(kOccupied | kReady), low, kh, kl);
-                    *reinterpret_cast<ulonglong2 *>(xkeys + 2 * o) = make_ulonglong2(kh, kl);
+                    *reinterpret_cast<Keys2 *>(xkeys + 2 * o) = Keys2{kh, kl};
                 }
                 xcounts[o] = cnt;
             }

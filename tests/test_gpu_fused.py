@@ -167,3 +167,27 @@ def test_fused_captured_replays_take_new_buffers():
             assert_same(host_sorted(keys, counts, n), wants[j], "fused replay, round %d" % rnd)
             last_n = n
         assert g.stats()["graph_replays"] > 0
+
+
+def test_fused_long_keys_at_any_word():
+    """The keys of a long-k graph go to an array that starts at an odd word (the
+    contract aligns the counters, not the keys)."""
+    k = 45
+    rng = np.random.default_rng(45)
+    rs = readsim.reads_from_strings([np.frombuffer(b"ACGT", np.uint8)[rng.integers(0, 4, 50_000)].tobytes()], k)
+    hi, lo, want = oracle.build_graph_wide(rs.reads, rs.offsets, k)
+    n = hi.shape[0]
+    print("[case] %d vertices, keys at byte 8 of a buffer" % n, flush=True)
+    keys = torch.full((2 * n + 3,), -1, dtype=torch.int64, device="cuda")
+    counts = torch.empty((n, 4), dtype=torch.int32, device="cuda")
+    with dbg.Graph(expected_vertices=n, flags=dbg.F_BINNED) as g:
+        out = keys[1:1 + 2 * n].view(n, 2)
+        assert out.data_ptr() % 16 == 8
+        assert g.build_extract_device(torch.from_numpy(rs.reads).cuda(), torch.from_numpy(rs.offsets.astype(np.int64)).cuda(),
+                                      k, out, counts) == n
+    got = keys.cpu().numpy()
+    assert got[0] == -1 and (got[1 + 2 * n:] == -1).all()
+    got = got[1:1 + 2 * n].view(np.uint64)
+    order = np.lexsort((got[1::2], got[::2]))
+    assert np.array_equal(got[::2][order], hi) and np.array_equal(got[1::2][order], lo)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32)[order], want)
