@@ -49,8 +49,8 @@ __device__ __forceinline__ void atomic_add_u64(uint64_t *p, uint64_t v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Instance owning a global read index: the last i with read_begin <= r.
-// The instance of read r, one of [lo, hi).
+// Instance owning a global read index: the last i of [lo, hi) with
+// read_begin <= r.
 __device__ __forceinline__ uint32_t instance_of_read(const Instance *inst, uint32_t lo, uint32_t hi, uint64_t r) {
     while (hi - lo > 1) {
         const uint32_t mid = (lo + hi) >> 1;

@@ -67,6 +67,64 @@ static void check_table_geometry() {
     }
 }
 
+// What the kernels of a pass by sorted tiles address stays within the capacities
+// and byte sizes reserved for it (sort_caps, SortSizes), for random tables,
+// inputs and skew: the tiles and groups of level 1, transposed offsets and group
+// sums of the two-level instances, and each bucket's tiles and records on whole
+// lines in level 2, with a pair of records stored at an odd end.
+static void check_sorted(std::mt19937_64 &rng) {
+    for (int round = 0; round < 4000; ++round) {
+        const uint32_t m = 1 + (uint32_t)(rng() % (round % 3 ? 6 : 200));
+        const uint64_t len = 64 + rng() % (round % 4 ? (1ull << 23) : (1ull << 32));
+        std::vector<Instance> in(m);
+        for (Instance &x : in) {
+            x = Instance{};
+            uint64_t parts = 0;
+            const uint64_t want = 1 + rng() % (rng() % 3 ? 3000 : 300000);
+            if (!dbgrt::table_geometry(want * dbgk::kSegSlots, rng() % 8 != 0, &x.d1, &x.fan, &parts)) continue;
+            x.parts = (uint32_t)parts;
+            x.k = m == 1 && round % 2 ? 45 : 21;
+            x.entry_words = x.k > 32 ? 4 : 3;
+        }
+        dbgk::BuildShape shape{256, 4, 0, 0};
+        const dbgrt::PassKey k = dbgrt::pass_key(m, 1 + rng() % len, len, shape, true, in.data(), dbgrt::PassOpts{});
+        CHECK(k.sorted, "round %d", round);
+        dbgk::SortBuffers sb{};
+        dbgrt::sort_caps(k, sb);
+        const dbgrt::SortSizes z(k, sb);
+        uint64_t tiles = 0, groups = 0, offt = 0, gsum = 0, buckets = 0, tiles2 = 0, at2 = 0, end2 = 0, left = len;
+        for (uint32_t i = 0; i < m; ++i) {
+            const uint64_t w = i + 1 == m ? left : (left ? rng() % (left + 1) : 0);  // its windows
+            left -= w;
+            const uint64_t t = (w + sb.tile1 - 1) / sb.tile1;
+            tiles += t;
+            CHECK(in[i].d1 + 1 <= sb.row1 && in[i].d1 <= sb.d1_max && in[i].fan + 1 <= sb.row2, "round %d: rows", round);
+            if (in[i].fan == 1) continue;
+            CHECK(sb.two_level && in[i].d1 <= k.d1_two_cap, "round %d: levels", round);
+            const uint64_t g = (t + dbgk::kSortGroup - 1) / dbgk::kSortGroup;
+            groups += g;
+            offt += t * in[i].d1;
+            gsum += g * in[i].d1;
+            buckets += in[i].d1;
+            uint64_t records = w;
+            for (uint32_t b = 0; b < in[i].d1; ++b) {
+                const uint64_t n = b + 1 == in[i].d1 ? records : std::min(records, rng() % (2 * (w / in[i].d1) + 2));
+                records -= n;
+                tiles2 += (n + sb.tile2 - 1) / sb.tile2;
+                end2 = std::max(end2, at2 + n + (n & 1));
+                at2 += (n + 15) & ~15ull;
+            }
+        }
+        CHECK(tiles <= sb.tiles1_cap && groups <= sb.groups_cap && buckets <= sb.buckets_cap && tiles2 <= sb.tiles2_cap,
+              "round %d: %llu tiles, %llu groups, %llu buckets, %llu tiles", round, (unsigned long long)tiles,
+              (unsigned long long)groups, (unsigned long long)buckets, (unsigned long long)tiles2);
+        CHECK(8 * tiles <= z.tile_read && 2 * tiles * sb.row1 <= z.off1 && 8 * k.rw * tiles * sb.tile1 <= z.rec1, "round %d: level 1", round);
+        CHECK(4 * offt <= z.offt && 4 * gsum <= z.gsum && 8 * gsum <= z.gpre, "round %d: between", round);
+        CHECK(2 * tiles2 * sb.row2 <= z.off2 && 8 * k.rw * end2 <= z.rec2, "round %d: level 2", round);
+        CHECK(buckets * sizeof(dbgk::SortBucket) <= z.buckets && (!buckets || 8 * (buckets + 1) <= z.tile2_base), "round %d: buckets", round);
+    }
+}
+
 // The search times no build twice (with automatic shapes chunks and divisor do
 // nothing), finds the best of what it times, and tunes the scatter's launch where
 // set shapes are the best.
@@ -244,6 +302,7 @@ int main() {
     check_host_counts(rng);
     check_chunks(rng);
     check_tuner(rng);
+    check_sorted(rng);
     if (failures) std::printf("%d failures\n", failures);
     else std::printf("ok\n");
     return failures > 100 ? 100 : failures;
