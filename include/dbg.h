@@ -204,11 +204,11 @@ int dbg_create(const dbg_config *cfg, dbg_graph **out);
 
 /* Add the k-mers of host-resident reads (makeGraph over all reads).  The
  * input is copied; the caller may free it on return.  Synchronous: returns
- * after the device work and the status readback.  Input of 32 MiB or more, and
- * results of 16 MiB or more of dbg_extract and dbg_extract_normalized, are
- * copied by up to six threads through 24 MiB of pinned host memory, which the
- * handles of a process share: up to four such areas a device stay pinned until
- * the last handle that made such a copy is destroyed.  Builds on one handle
+ * after the device work and the status readback.  From 16 MiB on, input and the
+ * results of dbg_extract and dbg_extract_normalized are copied by up to six
+ * threads through 24 MiB of pinned host memory, which the handles of a process
+ * share: up to four such areas a device stay pinned until the last handle that
+ * made such a copy is destroyed.  Builds on one handle
  * accumulate (counts add), and all must use the same k.  2 <= k <= 64; the
  * first build with k > 32 re-allocates the table with 32-byte entries (two
  * key words); binned graphs stay binned up to k = 63, and direct builds of

@@ -146,10 +146,11 @@ class PinnedWord {
 // reads and its 124 MB of vertices took 13.3 ms and now take 4.3.  Each copy
 // costs the stream 10 to 20 us, so that chunks of 1 MB give 5.2 ms and of 256 KB
 // 11; 4 MB give 4.1, and 4 ms more when the slots are pinned on first use.
-// Results under kSmall gain less than that first use costs.  Input has no fresh
-// pages, and the runtime's own copy keeps up with the threads for longer: builds
-// from 17 and 24 MB of reads took 1.10 and 1.53 ms with it and 1.14 and 1.53
-// with the slots, from 40 and 300 MB 2.7 and 20.3 against 2.4 and 16.7.
+// Under kSmall the gain is less than that first use costs.  Input has no fresh
+// pages, so that only the link's rate is to be had: builds from 17, 24, 40 and
+// 300 MB of reads take 1.11, 1.52, 2.70 and 20.3 ms with the runtime's own copy,
+// and 1.08, 1.46, 2.36 and 16.7 with the slots (1.14 and 1.53 for the smaller
+// while the caller started all workers before its first chunk).
 //
 // The slots belong to the process: a handle takes a set of them for the length
 // of one copy.  kIdle sets a device stay pinned between copies, as many as
@@ -162,7 +163,7 @@ class HostStage {
         void *dev;
         uint64_t bytes;
     };
-    static constexpr uint64_t kSmall = 16u << 20, kSmallIn = 32u << 20;
+    static constexpr uint64_t kSmall = 16u << 20;
 
     // All of the spans, in order of the stream.  Out: back when they have
     // arrived; in: back when the host's side has been read.
@@ -172,7 +173,7 @@ class HostStage {
             bytes += spans[i].bytes;
             chunks += (spans[i].bytes + kChunk - 1) / kChunk;
         }
-        Slots *const slots = bytes < (out ? kSmall : kSmallIn) ? nullptr : take(device);
+        Slots *const slots = bytes < kSmall ? nullptr : take(device);
         if (!slots) {
             for (uint32_t i = 0; i < n; ++i) {
                 if (!spans[i].bytes) continue;
@@ -207,17 +208,23 @@ class HostStage {
             }
             if (e != hipSuccess) error.store(e, std::memory_order_relaxed);
         };
-        {
-            std::thread threads[kWorkers - 1];
-            const uint32_t want = (uint32_t)std::min<uint64_t>({kWorkers, (chunks + 1) / 2, std::max(2u, std::thread::hardware_concurrency()) / 2});
+        const uint32_t want = (uint32_t)std::min<uint64_t>({kWorkers, (chunks + 1) / 2, std::max(2u, std::thread::hardware_concurrency()) / 2});
+        // Results: all workers start at once, as each brings pages in.  Input: the link
+        // is busy with the first chunk already, and each worker starts the next.
+        const auto crew = [&](const auto &self, uint32_t w) -> void {
+            std::thread started[kWorkers];
             try {
-                for (uint32_t w = 1; w < want; ++w) threads[w - 1] = std::thread(work, w);
+                for (uint32_t x = w + 1; x < want && (!out || w == 0); ++x) {
+                    started[x] = std::thread([&self, x] { self(self, x); });
+                    if (!out) break;
+                }
             } catch (...) {  // no more threads: those there are take all chunks
             }
-            work(0);
-            for (auto &t : threads)
+            work(w);
+            for (auto &t : started)
                 if (t.joinable()) t.join();
-        }
+        };
+        crew(crew, 0);
         const hipError_t e = static_cast<hipError_t>(error.load());
         if (e != hipSuccess) (void)hipStreamSynchronize(s);  // nothing still moves when the caller hears of it
         give(slots);
