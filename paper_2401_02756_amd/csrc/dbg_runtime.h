@@ -143,7 +143,7 @@ class PinnedWord {
 // side of their slot while the link fills or drains the other of their two.
 // The runtime's own copy of such memory moves 12 GB/s on one thread, which also
 // meets the first touch of every page of a fresh result: a build from 20 MB of
-// reads and its 124 MB of vertices took 13.3 ms and now take 4.3.  Each copy
+// reads and its 124 MB of vertices took 13.3 ms and now takes 4.3 to 4.6.  Each copy
 // costs the stream 10 to 20 us, so that chunks of 1 MB give 5.2 ms and of 256 KB
 // 11; 4 MB give 4.1, and 4 ms more when the slots are pinned on first use.
 // Under kSmall the gain is less than that first use costs.  Input has no fresh
